@@ -2,12 +2,11 @@
 // role, with an MLP): 10 Table I features -> 32 -> 32 -> 2 (tanh hidden
 // layers, linear output = predicted log t_EIG and log t_ALS of one mode).
 // Training runs on the device with these kernels:
-//   forward    one thread per sample: normalized features, both hidden
-//              layers and the output, kept for the backward pass;
-//   backward   one thread per sample: output and hidden deltas of the loss
-//              L = 0.5/B * sum (Y - T)^2;
-//   gradient   one thread per parameter: the sum over samples of
-//              delta x activation, in sample order (deterministic);
+//   loss/grad  each workgroup takes MS samples through the forward pass, the
+//              deltas of L = 0.5/B * sum (Y - T)^2 and the products
+//              delta x activation, and writes one partial gradient and loss;
+//   reduce     the partial gradients and losses, in workgroup order with
+//              FP64 sums (deterministic);
 //   Adam       one thread per parameter.
 // Parameter packing (float): W1 (32x10, column-major), b1 (32), W2 (32x32),
 // b2 (32), W3 (2x32), b3 (2), then the feature normalization mu (10) and
@@ -26,23 +25,18 @@ constexpr int NTRAIN = OMU;  // trainable parameters
 }  // namespace
 
 __global__ void mlp_forward_kernel(const float *__restrict__ w, int64_t B, const float *__restrict__ X,
-                                   float *__restrict__ XN, float *__restrict__ H1,
-                                   float *__restrict__ H2, float *__restrict__ Y) {
+                                   float *__restrict__ Y) {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= B) return;
     float xn[NI], h1[NH], h2[NH];
 #pragma unroll
-    for (int k = 0; k < NI; ++k) {
-        xn[k] = (X[k + NI * s] - w[OMU + k]) * w[OISD + k];
-        XN[k + NI * s] = xn[k];
-    }
+    for (int k = 0; k < NI; ++k) xn[k] = (X[k + NI * s] - w[OMU + k]) * w[OISD + k];
 #pragma unroll
     for (int o = 0; o < NH; ++o) {
         float z = w[OB1 + o];
 #pragma unroll
         for (int k = 0; k < NI; ++k) z += w[OW1 + o + NH * k] * xn[k];
         h1[o] = tanhf(z);
-        H1[o + NH * s] = h1[o];
     }
 #pragma unroll
     for (int o = 0; o < NH; ++o) {
@@ -50,7 +44,6 @@ __global__ void mlp_forward_kernel(const float *__restrict__ w, int64_t B, const
 #pragma unroll
         for (int k = 0; k < NH; ++k) z += w[OW2 + o + NH * k] * h1[k];
         h2[o] = tanhf(z);
-        H2[o + NH * s] = h2[o];
     }
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
@@ -61,78 +54,156 @@ __global__ void mlp_forward_kernel(const float *__restrict__ w, int64_t B, const
     }
 }
 
-__global__ void mlp_backward_kernel(const float *__restrict__ w, int64_t B, const float *__restrict__ H1,
-                                    const float *__restrict__ H2, const float *__restrict__ Y,
-                                    const float *__restrict__ T, float *__restrict__ D1,
-                                    float *__restrict__ D2, float *__restrict__ D3) {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= B) return;
-    float d3[NO], d2[NH];
-    const float invB = 1.0f / (float)B;
+// Loss and gradient of MS samples per workgroup.  Bound by latency: a sample
+// is 1.4 k multiply-adds, a batch of thousands of samples 40 MFLOP, so the
+// work is spread until every workgroup has a few microseconds of it.  A group
+// of NH lanes carries one sample, lane o holding neuron o: its rows and
+// columns of W2 stay in registers, the sample's activations and deltas cross
+// LDS as broadcasts.  Then the 256 threads each own 4 entries of the W2
+// gradient (and their share of the rest) and sum delta x activation over the
+// MS samples from LDS.  The gradient kept in one thread per parameter, each
+// walking all samples serially in 6 workgroups, took 1505 us of a 1.55 ms
+// step at 4499 samples; the whole step (this, the reduction, Adam) takes 23 us.
+// MS = 32: 16 samples doubles the partial gradients to write and read, 64
+// leaves half the chip without a workgroup at a few thousand samples.
+constexpr int MS = 32, MG = 256 / NH;
+// floats of one partial: the trained parameters, then the loss sum (a double)
+constexpr int MPART = NTRAIN + 2;
+static_assert(NTRAIN % 2 == 0, "the loss sum is 8-byte aligned");
+
+__device__ __forceinline__ float mlp_dot(const float (&w)[NH], const float *__restrict__ v, float z) {
 #pragma unroll
-    for (int o = 0; o < NO; ++o) {
-        d3[o] = (Y[o + NO * s] - T[o + NO * s]) * invB;
-        D3[o + NO * s] = d3[o];
+    for (int k = 0; k < NH; k += 4) {
+        const float4 t = *reinterpret_cast<const float4 *>(v + k);
+        z += w[k] * t.x;
+        z += w[k + 1] * t.y;
+        z += w[k + 2] * t.z;
+        z += w[k + 3] * t.w;
     }
-#pragma unroll
-    for (int k = 0; k < NH; ++k) {
-        float a = 0.0f;
-#pragma unroll
-        for (int o = 0; o < NO; ++o) a += w[OW3 + o + NO * k] * d3[o];
-        const float h = H2[k + NH * s];
-        d2[k] = a * (1.0f - h * h);
-        D2[k + NH * s] = d2[k];
-    }
-#pragma unroll
-    for (int k = 0; k < NH; ++k) {
-        float a = 0.0f;
-#pragma unroll
-        for (int o = 0; o < NH; ++o) a += w[OW2 + o + NH * k] * d2[o];
-        const float h = H1[k + NH * s];
-        D1[k + NH * s] = a * (1.0f - h * h);
-    }
+    return z;
 }
 
-// grad[p] = sum_s delta(s) * activation(s) for the parameter p (sample order).
-__global__ void mlp_grad_kernel(int64_t B, const float *__restrict__ XN, const float *__restrict__ H1,
-                                const float *__restrict__ H2, const float *__restrict__ D1,
-                                const float *__restrict__ D2, const float *__restrict__ D3,
-                                float *__restrict__ grad) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= SEL_NPARAM) return;
-    const float *d = nullptr, *a = nullptr;
-    int dn = 0, an = 0, o = 0, k = 0;
-    if (p < OB1) { dn = NH; an = NI; d = D1; a = XN; o = (p - OW1) % NH; k = (p - OW1) / NH; }
-    else if (p < OW2) { dn = NH; d = D1; o = p - OB1; }
-    else if (p < OB2) { dn = NH; an = NH; d = D2; a = H1; o = (p - OW2) % NH; k = (p - OW2) / NH; }
-    else if (p < OW3) { dn = NH; d = D2; o = p - OB2; }
-    else if (p < OB3) { dn = NO; an = NH; d = D3; a = H2; o = (p - OW3) % NO; k = (p - OW3) / NO; }
-    else if (p < OMU) { dn = NO; d = D3; o = p - OB3; }
-    else { grad[p] = 0.0f; return; }  // normalization constants are not trained
-    float acc = 0.0f;
-    if (a) {
-        for (int64_t s = 0; s < B; ++s) acc += d[o + dn * s] * a[k + an * s];
-    } else {
-        for (int64_t s = 0; s < B; ++s) acc += d[o + dn * s];
+// One workgroup per MS samples.  part: MPART floats per workgroup, or null
+// (a single workgroup): the sums go to grad and loss directly.
+__global__ __launch_bounds__(256) void mlp_grad_kernel(const float *__restrict__ w, int64_t B,
+                                                       const float *__restrict__ X, const float *__restrict__ T,
+                                                       float *__restrict__ part, float *__restrict__ grad,
+                                                       float *__restrict__ loss) {
+    __shared__ __align__(16) float s_x[MS][12], s_h1[MS][NH], s_h2[MS][NH], s_d1[MS][NH], s_d2[MS][NH], s_d3[MS][NO];
+    __shared__ double s_l[MS];
+    const int tid = threadIdx.x, o = tid % NH, grp = tid / NH;
+    const int64_t s0 = (int64_t)blockIdx.x * MS;
+    const int ns = (int)(B - s0 < MS ? B - s0 : MS);
+    float w1[NI], wr[NH], wc[NH];
+#pragma unroll
+    for (int k = 0; k < NI; ++k) w1[k] = w[OW1 + o + NH * k];
+#pragma unroll
+    for (int k = 0; k < NH; ++k) {
+        wr[k] = w[OW2 + o + NH * k];   // row o (forward)
+        wc[k] = w[OW2 + k + NH * o];   // column o (backward)
     }
-    grad[p] = acc;
-}
-
-__global__ void mlp_loss_kernel(int64_t B, const float *__restrict__ Y, const float *__restrict__ T,
-                                float *__restrict__ loss) {
-    __shared__ double red[256];
-    double acc = 0.0;
-    for (int64_t e = threadIdx.x; e < B * NO; e += 256) {
-        const double r = (double)Y[e] - (double)T[e];
-        acc += r * r;
+    const float b1 = w[OB1 + o], b2 = w[OB2 + o];
+    const float w30 = w[OW3 + NO * o], w31 = w[OW3 + 1 + NO * o];
+    for (int e = tid; e < MS * NI; e += 256) {
+        const int sl = e / NI, k = e - sl * NI;
+        s_x[sl][k] = sl < ns ? (X[k + NI * (s0 + sl)] - w[OMU + k]) * w[OISD + k] : 0.f;
     }
-    red[threadIdx.x] = acc;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
+    // the groups are halves of a wave: a wave's own LDS writes are visible to
+    // it in order, so only the compiler needs the fences between the layers
+    for (int sl = grp; sl < MS; sl += MG) {
+        float z = b1;
+#pragma unroll
+        for (int k = 0; k < NI; ++k) z += w1[k] * s_x[sl][k];
+        const float h1 = sl < ns ? tanhf(z) : 0.f;   // samples past the batch contribute nothing
+        s_h1[sl][o] = h1;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const float h2 = sl < ns ? tanhf(mlp_dot(wr, s_h1[sl], b2)) : 0.f;
+        s_h2[sl][o] = h2;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (o < NO) {
+            float y = w[OB3 + o];
+            for (int k = 0; k < NH; ++k) y += w[OW3 + o + NO * k] * s_h2[sl][k];
+            const float r = sl < ns ? y - T[o + NO * (s0 + (sl < ns ? sl : 0))] : 0.f;
+            s_d3[sl][o] = r * (1.0f / (float)B);
+            const double r2 = (double)r * (double)r;
+            const double both = r2 + __shfl_xor(r2, 1);
+            if (o == 0) s_l[sl] = both;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const float d2 = sl < ns ? (w30 * s_d3[sl][0] + w31 * s_d3[sl][1]) * (1.0f - h2 * h2) : 0.f;
+        s_d2[sl][o] = d2;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        s_d1[sl][o] = sl < ns ? mlp_dot(wc, s_d2[sl], 0.f) * (1.0f - h1 * h1) : 0.f;
     }
-    if (threadIdx.x == 0) *loss = (float)(0.5 * red[0] / (double)B);
+    __syncthreads();
+    float *const out = part ? part + (int64_t)blockIdx.x * MPART : grad;
+    // W2: rows o, columns 4 grp .. 4 grp + 3 (samples past ns have zero deltas)
+    static_assert(MG * 4 == NH, "four columns per group");
+    float a[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int sl = 0; sl < MS; ++sl) {
+        const float d = s_d2[sl][o];
+        const float4 h = *reinterpret_cast<const float4 *>(&s_h1[sl][4 * grp]);
+        a[0] += d * h.x;
+        a[1] += d * h.y;
+        a[2] += d * h.z;
+        a[3] += d * h.w;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) out[OW2 + o + NH * (4 * grp + c)] = a[c];
+    // W1 (rows o, columns grp, grp + MG), the biases and W3
+    for (int k = grp; k < NI; k += MG) {
+        float g = 0.f;
+#pragma unroll 8
+        for (int sl = 0; sl < MS; ++sl) g += s_d1[sl][o] * s_x[sl][k];
+        out[OW1 + o + NH * k] = g;
+    }
+    float g = 0.f;
+    if (grp == 2) {
+        for (int sl = 0; sl < MS; ++sl) g += s_d1[sl][o];
+        out[OB1 + o] = g;
+    } else if (grp == 3) {
+        for (int sl = 0; sl < MS; ++sl) g += s_d2[sl][o];
+        out[OB2 + o] = g;
+    } else if (grp == 4 || grp == 5) {
+        for (int sl = 0; sl < MS; ++sl) g += s_d3[sl][grp - 4] * s_h2[sl][o];
+        out[OW3 + (grp - 4) + NO * o] = g;
+    } else if (grp == 6 && o < NO) {
+        for (int sl = 0; sl < MS; ++sl) g += s_d3[sl][o];
+        out[OB3 + o] = g;
+    } else if (grp == 7 && o == 0) {
+        double l = 0.0;
+        for (int sl = 0; sl < ns; ++sl) l += s_l[sl];
+        if (part) *reinterpret_cast<double *>(out + NTRAIN) = l;
+        else if (loss) *loss = (float)(0.5 * l / (double)B);
+    }
+    if (!part)
+        for (int p = NTRAIN + tid; p < SEL_NPARAM; p += 256) grad[p] = 0.f;
+}
+
+// grad = the partial gradients summed over the np workgroups (64 parameters
+// per workgroup, four waves on interleaved partials, FP64 sums combined in a
+// fixed order), the normalization entries zero; loss from the partial sums.
+__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float *__restrict__ part, int np, int64_t B,
+                                                         float *__restrict__ grad, float *__restrict__ loss) {
+    __shared__ double s_sum[4][64];
+    const int el = threadIdx.x & 63, ks = threadIdx.x >> 6;
+    const int p = blockIdx.x * 64 + el;
+    const bool is_loss = p == SEL_NPARAM;   // one past the parameters: the loss
+    double acc = 0.0;
+    if (p < NTRAIN) {
+#pragma unroll 8
+        for (int k = ks; k < np; k += 4) acc += (double)part[(int64_t)k * MPART + p];
+    } else if (is_loss) {
+        for (int k = ks; k < np; k += 4) acc += *reinterpret_cast<const double *>(part + (int64_t)k * MPART + NTRAIN);
+    }
+    s_sum[ks][el] = acc;
+    __syncthreads();
+    if (ks != 0) return;
+    const double sum = (s_sum[0][el] + s_sum[1][el]) + (s_sum[2][el] + s_sum[3][el]);
+    if (p < SEL_NPARAM) grad[p] = p < NTRAIN ? (float)sum : 0.f;
+    else if (is_loss && loss) *loss = (float)(0.5 * sum / (double)B);
 }
 
 __global__ void adam_kernel(float *__restrict__ w, const float *__restrict__ g, float *__restrict__ m,
@@ -148,44 +219,28 @@ __global__ void adam_kernel(float *__restrict__ w, const float *__restrict__ g, 
     w[p] -= lr * (mp * c1) / (sqrtf(vp * c2) + eps);
 }
 
+// workspace floats per sample: more than the partial gradients take
+constexpr int64_t MLP_WS_FLOATS = NI + 2 * NH + NO + 2 * NH + NO;
 size_t mlp_ws_bytes(int64_t B) {
-    return (size_t)B * (NI + 2 * NH + NO + 2 * NH + NO) * sizeof(float) + 256;
+    return (size_t)B * MLP_WS_FLOATS * sizeof(float) + 256;
 }
-
-namespace {
-struct MlpWs {
-    float *XN, *H1, *H2, *Y, *D1, *D2, *D3;
-};
-MlpWs mlp_layout(void *ws, int64_t B) {
-    MlpWs m;
-    float *p = (float *)ws;
-    m.XN = p; p += NI * B;
-    m.H1 = p; p += NH * B;
-    m.H2 = p; p += NH * B;
-    m.Y = p; p += NO * B;
-    m.D1 = p; p += NH * B;
-    m.D2 = p; p += NH * B;
-    m.D3 = p;
-    return m;
-}
-}  // namespace
 
 hipError_t mlp_forward_launch(const float *w, int64_t B, const float *X, float *Y, void *ws, hipStream_t s) {
-    MlpWs m = mlp_layout(ws, B);
     const unsigned g = (unsigned)((B + 255) / 256);
-    hipLaunchKernelGGL(mlp_forward_kernel, dim3(g), dim3(256), 0, s, w, B, X, m.XN, m.H1, m.H2, Y ? Y : m.Y);
+    hipLaunchKernelGGL(mlp_forward_kernel, dim3(g), dim3(256), 0, s, w, B, X, Y);
     return hipGetLastError();
 }
 
 hipError_t mlp_loss_grad_launch(const float *w, int64_t B, const float *X, const float *T, float *grad,
                                 float *loss, void *ws, hipStream_t s) {
-    MlpWs m = mlp_layout(ws, B);
-    const unsigned g = (unsigned)((B + 255) / 256);
-    hipLaunchKernelGGL(mlp_forward_kernel, dim3(g), dim3(256), 0, s, w, B, X, m.XN, m.H1, m.H2, m.Y);
-    hipLaunchKernelGGL(mlp_backward_kernel, dim3(g), dim3(256), 0, s, w, B, m.H1, m.H2, m.Y, T, m.D1, m.D2, m.D3);
-    hipLaunchKernelGGL(mlp_grad_kernel, dim3((SEL_NPARAM + 255) / 256), dim3(256), 0, s, B, m.XN, m.H1, m.H2,
-                       m.D1, m.D2, m.D3, grad);
-    if (loss) hipLaunchKernelGGL(mlp_loss_kernel, dim3(1), dim3(256), 0, s, B, m.Y, T, loss);
+    const int64_t np = (B + MS - 1) / MS;
+    float *part = np > 1 ? (float *)ws : nullptr;   // np MPART floats, below mlp_ws_bytes(B) for B > MS
+    static_assert((int64_t)2 * MPART <= (int64_t)(MS + 1) * MLP_WS_FLOATS && MPART <= MS * MLP_WS_FLOATS,
+                  "the partial gradients fit the workspace");
+    hipLaunchKernelGGL(mlp_grad_kernel, dim3((unsigned)np), dim3(256), 0, s, w, B, X, T, part, grad, loss);
+    if (np > 1)
+        hipLaunchKernelGGL(mlp_reduce_kernel, dim3((SEL_NPARAM + 64) / 64), dim3(256), 0, s, part, (int)np, B, grad,
+                           loss);
     return hipGetLastError();
 }
 
