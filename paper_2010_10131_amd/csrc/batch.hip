@@ -441,8 +441,7 @@ __device__ bool bsi_solve(const double *S, int n, int R, int p, double s_unit, d
     __syncthreads();
     bsi_tn<false>(p, p, n, w.Q, w.Z, w.T);
     __syncthreads();
-    if (teig_z_fits(p, R, true)) teig_body<true, true>(w.T, p, p, R, w.W, p, w.th, false, w.te, flag);
-    else teig_body<true, false>(w.T, p, p, R, w.W, p, w.th, false, w.te, flag);
+    teig_small(w.T, p, p, R, w.W, p, w.th, false, w.te, flag);
     __syncthreads();
     // U = Q W and V = Z W on the matrix cores (V in Z2), then per vector
     // (one wave each) the Ritz residual ||V(:, r) - theta_r U(:, r)|| and the
@@ -497,7 +496,7 @@ __global__ __launch_bounds__(BE_THREADS) void batch_eig_kernel(const BatchStep *
     const int n = (int)d.I, R = (int)d.R;
     const double *S = (const double *)(ws + d.S_off);
     double *U = Up[(int64_t)d.tensor * order + mode];
-    const bool alds = n <= TE_LDS_N, zlds = teig_z_fits(n, R, alds);
+    const bool alds = n <= TE_LDS_N;
     double *const base = (double *)(ws + d.eig_off);
     const TeScratch sc = teig_scratch_layout(base, n, R, alds);
     if (d.sib > 0) {
@@ -508,13 +507,9 @@ __global__ __launch_bounds__(BE_THREADS) void batch_eig_kernel(const BatchStep *
             return;
         if (threadIdx.x == 0 && flag) atomicAdd((unsigned long long *)(flag + 1), 1ull);   // direct solves taken
     }
-    if (alds) {
-        if (zlds) teig_body<true, true>(S, n, n, R, U, n, nullptr, true, sc, flag);
-        else teig_body<true, false>(S, n, n, R, U, n, nullptr, true, sc, flag);
-    } else {
-        if (zlds) teig_body<false, true>(S, n, n, R, U, n, nullptr, true, sc, flag);
-        else teig_body<false, false>(S, n, n, R, U, n, nullptr, true, sc, flag);
-    }
+    if (alds) teig_small(S, n, n, R, U, n, nullptr, true, sc, flag);
+    else if (teig_z_fits(n, R)) teig_body<true>(S, n, n, R, U, n, nullptr, true, sc, flag);
+    else teig_body<false>(S, n, n, R, U, n, nullptr, true, sc, flag);
 }
 
 // --------------------------------------------------- grouped split / TTM
@@ -598,10 +593,9 @@ int64_t batch_si_block(int64_t n, int64_t R, int64_t rank_bound) {
 }
 
 size_t batch_eig_lds(int64_t n, int64_t R, int64_t p) {
-    const bool alds = n <= TE_LDS_N;
-    size_t b = teig_lds_bytes(n, R, alds, teig_z_fits(n, R, alds), teig_v_keep(n, R, alds));
+    size_t b = teig_lds_bytes(n, R);
     if (p > 0) {
-        b = std::max(b, teig_lds_bytes(p, R, true, teig_z_fits(p, R, true), teig_v_keep(p, R, true)));
+        b = std::max(b, teig_lds_bytes(p, R));
         b = std::max(b, chol_lds_bytes(p));
         b = std::max(b, bsi_stage_bytes(p));
     }

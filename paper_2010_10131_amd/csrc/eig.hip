@@ -91,7 +91,8 @@ __global__ void sign_fix_kernel(double *__restrict__ U, int n, int R) {
         for (int i = threadIdx.x; i < n; i += blockDim.x) U[i + (int64_t)n * r] = -U[i + (int64_t)n * r];
 }
 
-template <bool ALDS, bool ZLDS>
+// SMALL: n <= TE_LDS_N (teig_small); ZLDS: see teig_body
+template <bool SMALL, bool ZLDS>
 __global__ __launch_bounds__(TE_T) void teig_kernel(const double *__restrict__ S, int64_t lds, int n, int R,
                                                    double *__restrict__ U, int64_t ldu,
                                                    double *__restrict__ lam, int sign_rule, TeScratch sc,
@@ -101,7 +102,8 @@ __global__ __launch_bounds__(TE_T) void teig_kernel(const double *__restrict__ S
     // chk_tol * chk[R] or is not finite; count records that it ran
     if (!gate_open(chk, R, chk_tol)) return;
     if (chk && count && threadIdx.x == 0) *count += 1;
-    teig_body<ALDS, ZLDS>(S, lds, n, R, U, ldu, lam, sign_rule != 0, sc, flag);
+    if constexpr (SMALL) teig_small(S, lds, n, R, U, ldu, lam, sign_rule != 0, sc, flag);
+    else teig_body<ZLDS>(S, lds, n, R, U, ldu, lam, sign_rule != 0, sc, flag);
 }
 
 // ---- subspace-iteration products: one 16 x 16 tile of C per workgroup on
@@ -448,11 +450,11 @@ hipError_t jacobi_launch(int64_t n, int64_t R, const double *S, double *U, doubl
     return hipGetLastError();
 }
 
-template <bool ALDS, bool ZLDS>
+template <bool SMALL, bool ZLDS>
 hipError_t teig_go(const double *S, int64_t lds, int64_t n, int64_t R, double *U, int64_t ldu, double *lam,
                    bool sign_rule, TeScratch sc, int64_t *flag, const double *chk, double chk_tol, int64_t *count,
                    size_t lds_b, hipStream_t s) {
-    auto k = teig_kernel<ALDS, ZLDS>;
+    auto k = teig_kernel<SMALL, ZLDS>;
     if (hipError_t ea = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_b))
         return ea;
     hipLaunchKernelGGL(k, dim3(1), dim3(TE_T), lds_b, s, S, lds, (int)n, (int)R, U, ldu, lam, sign_rule ? 1 : 0, sc,
@@ -462,21 +464,16 @@ hipError_t teig_go(const double *S, int64_t lds, int64_t n, int64_t R, double *U
 
 }  // namespace
 
-// Direct solver (teig_body.h) on the n x n matrix S: the matrix in LDS up to
-// order TE_LDS_N, in the scratch above; scratch holds teig_bytes(n, R).
+// Direct solver (teig_body.h) on the n x n matrix S; scratch holds
+// teig_bytes(n, R).
 hipError_t teig_launch(const double *S, int64_t lds, int64_t n, int64_t R, double *U, int64_t ldu, double *lam,
                        bool sign_rule, void *scratch, int64_t *flag, const double *chk, double chk_tol,
                        int64_t *count, hipStream_t s) {
-    const bool alds = n <= TE_LDS_N;
-    const bool zlds = teig_z_fits(n, R, alds);
-    const TeScratch sc = teig_scratch_layout((double *)scratch, n, R, alds);
-    const size_t lb = teig_lds_bytes(n, R, alds, zlds, teig_v_keep(n, R, alds));
-    if (alds) {
-        return zlds ? teig_go<true, true>(S, lds, n, R, U, ldu, lam, sign_rule, sc, flag, chk, chk_tol, count, lb, s)
-                    : teig_go<true, false>(S, lds, n, R, U, ldu, lam, sign_rule, sc, flag, chk, chk_tol, count, lb, s);
-    }
-    return zlds ? teig_go<false, true>(S, lds, n, R, U, ldu, lam, sign_rule, sc, flag, chk, chk_tol, count, lb, s)
-                : teig_go<false, false>(S, lds, n, R, U, ldu, lam, sign_rule, sc, flag, chk, chk_tol, count, lb, s);
+    const TeScratch sc = teig_scratch_layout((double *)scratch, n, R, n <= TE_LDS_N);
+    const size_t lb = teig_lds_bytes(n, R);
+    if (n <= TE_LDS_N) return teig_go<true, true>(S, lds, n, R, U, ldu, lam, sign_rule, sc, flag, chk, chk_tol, count, lb, s);
+    return teig_z_fits(n, R) ? teig_go<false, true>(S, lds, n, R, U, ldu, lam, sign_rule, sc, flag, chk, chk_tol, count, lb, s)
+                             : teig_go<false, false>(S, lds, n, R, U, ldu, lam, sign_rule, sc, flag, chk, chk_tol, count, lb, s);
 }
 
 size_t eig_ws_bytes(int64_t n) {

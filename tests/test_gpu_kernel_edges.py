@@ -38,3 +38,28 @@ def test_mlp_gradient_at_workgroup_edges(api, B):
     go = np.concatenate([dW[0].T.ravel(), db[0], dW[1].T.ravel(), db[1], dW[2].T.ravel(), db[2], np.zeros(20)])
     assert abs(float(loss.item()) - lo) <= 1e-5 * lo
     np.testing.assert_allclose(grad.cpu().numpy(), go, rtol=0, atol=2e-5 * np.abs(go).max())
+
+
+@pytest.mark.parametrize("spectrum", ["graded", "clustered"])
+@pytest.mark.parametrize("n,R", [(1, 1), (2, 2), (3, 2), (4, 4), (17, 16), (18, 17), (49, 8), (63, 63), (64, 64),
+                                 (65, 64), (65, 65), (80, 64), (81, 33), (96, 96), (113, 65), (127, 127),
+                                 (128, 1), (128, 100), (128, 128)])
+def test_direct_solver_orders(api, n, R, spectrum):
+    """The direct solver of the decompositions at the edges of its register
+    layout (64 rows a wave, 16-column tiles, 16-reflector blocks, blocks that do
+    or do not fit the LDS): a 2-way FP64 tensor whose mode-1 Gram has known
+    eigenvalues, some of them equal.  Residual and orthogonality of a
+    backward-stable solver: a few n eps ||S||, here within 8 n eps."""
+    rng = np.random.default_rng(n * 131 + R)
+    Q = np.linalg.qr(rng.standard_normal((n, n)))[0]
+    sv = 0.9 ** np.arange(n) if spectrum == "graded" else 1.0 / (1.0 + np.arange(n) // 3)
+    Y = np.asfortranarray(Q * sv)
+    S = Y @ Y.T
+    _, U, ev, _ = api.mode_step(api.to_device(Y), 0, R, "eig", "fp64", "fp64")
+    U, ev = api.to_numpy(U), ev.cpu().numpy()
+    tol = 8 * n * 2.2e-16
+    np.testing.assert_allclose(ev, np.sort(sv ** 2)[::-1][:R], rtol=0, atol=max(tol, 1e-15))
+    assert np.linalg.norm(S @ U - U * ev, 2) <= max(tol, 1e-15)
+    np.testing.assert_allclose(U.T @ U, np.eye(R), rtol=0, atol=max(tol, 1e-15))
+    top = np.abs(U).argmax(0)
+    assert np.all(U[top, np.arange(R)] > 0)
