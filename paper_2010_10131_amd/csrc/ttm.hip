@@ -117,6 +117,77 @@ __global__ __launch_bounds__(64 * KS_WAVES) void ttm_ks_kernel(
                                             gridDim.x, blockIdx.y);
 }
 
+// Long contraction over few rows (FP64 products): the general kernel gives a
+// wave 16 NT rows and the whole of K, so a first mode of 30648 entries over
+// 2256 rows ran on 9 workgroups (2.2 ms for 553 MB).  Here the eight waves of
+// a workgroup share 16 rows: wave w takes the chunks w, w + 8, ... (the
+// workgroup streams 2 KB of each row per pass), with the next two chunks of
+// rows and factor in flight, and the eight partial tiles are summed in LDS in
+// wave order.  Bound by HBM with one workgroup on each of 141 of the 256 CUs:
+// 2187 -> 190 us (2.9 TB/s).  FP64 accumulation only: an FP32 sum over K keeps its order.
+constexpr int KW_WAVES = 8;
+template <typename T, int RTB, bool CONTIG>
+__global__ __launch_bounds__(64 * KW_WAVES) void ttm_kw_kernel(const T *__restrict__ Y, const uint4 *__restrict__ Uq,
+                                                              T *__restrict__ Z, int64_t L, int64_t K,
+                                                              int64_t Rout, int64_t P, int nchunks, int ntiles) {
+    constexpr int NQ = Frag<P_FP64>::NQ;
+    __shared__ f64x4 s_acc[KW_WAVES - 1][RTB][64];
+    if (CONTIG) L = 1;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
+    const int rt0 = blockIdx.y * RTB;
+    const int64_t p = (int64_t)blockIdx.x * 16 + (lane & 15);
+    const int64_t pc = p < P ? p : P - 1, b = pc / L, a = pc - b * L;
+    const int64_t base = a + L * K * b;
+    f64x4 acc[RTB];
+#pragma unroll
+    for (int rt = 0; rt < RTB; ++rt) acc[rt] = f64x4{0, 0, 0, 0};
+    T x[2][8];
+    FragQ<P_FP64> u[2][RTB];
+    auto load = [&](int c, T (&xs)[8], FragQ<P_FP64> (&us)[RTB]) {
+        ttm_load_chunk<T, CONTIG>(Y, base, L, K, (int64_t)c * KC + 8 * g, xs);
+#pragma unroll
+        for (int rt = 0; rt < RTB; ++rt) {
+            const int rtg = rt0 + rt < ntiles ? rt0 + rt : ntiles - 1;
+            const uint4 *src = Uq + (((int64_t)c * ntiles + rtg) * NQ) * 64 + lane;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) us[rt].q[q] = src[q * 64];
+        }
+    };
+    auto multiply = [&](const T (&xs)[8], const FragQ<P_FP64> (&us)[RTB]) {
+        Frag<P_FP64> yb;
+        make_frag(xs, yb);
+#pragma unroll
+        for (int rt = 0; rt < RTB; ++rt) mma_frag(us[rt].f, yb, acc[rt]);
+    };
+    int c = wave;
+    if (c < nchunks) load(c, x[0], u[0]);
+    if (c + KW_WAVES < nchunks) load(c + KW_WAVES, x[1], u[1]);
+    for (; c < nchunks; c += 2 * KW_WAVES) {
+        multiply(x[0], u[0]);
+        if (c + 2 * KW_WAVES < nchunks) load(c + 2 * KW_WAVES, x[0], u[0]);
+        if (c + KW_WAVES < nchunks) {
+            multiply(x[1], u[1]);
+            if (c + 3 * KW_WAVES < nchunks) load(c + 3 * KW_WAVES, x[1], u[1]);
+        }
+    }
+    if (wave > 0)
+#pragma unroll
+        for (int rt = 0; rt < RTB; ++rt) s_acc[wave - 1][rt][lane] = acc[rt];
+    __syncthreads();
+    if (wave > 0 || p >= P) return;
+    const int64_t zoff = a + L * Rout * b;
+#pragma unroll
+    for (int rt = 0; rt < RTB; ++rt) {
+#pragma unroll
+        for (int w = 0; w < KW_WAVES - 1; ++w) acc[rt] += s_acc[w][rt][lane];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int64_t r = (int64_t)(rt0 + rt) * 16 + drow<P_FP64>(g, v);
+            if (r < Rout) Z[zoff + L * r] = (T)acc[rt][v];
+        }
+    }
+}
+
 // Scratch for callers that cannot allocate (ttm_mode_n_noalloc): the
 // pre-split factor of one call lives here instead of in a caller workspace.
 // Each device that runs the library holds its own copy until the process
@@ -237,6 +308,23 @@ hipError_t launch_ttm_r(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K,
         if (contig && nchunks > 8 && nchunks <= 16)
             return launch_ttm_ks<PREC, 2>(reinterpret_cast<const float *>(Y), Uq, reinterpret_cast<float *>(Z),
                                           K, Rout, M, s);
+    }
+    if constexpr (PREC == P_FP64) {
+        // few rows and a long contraction: the eight waves of a workgroup split
+        // K (at least four chunks each) where the general kernel would leave
+        // CUs without a workgroup
+        constexpr int NTG = RTB == 1 ? 2 : 1;
+        const int64_t P = L * M, ntiles = (Rout + 15) / 16, nrb = (ntiles + RTB - 1) / RTB;
+        if (nchunks >= 4 * KW_WAVES && (P + 16 * NTG * TTM_WAVES - 1) / (16 * NTG * TTM_WAVES) * nrb < device_cu_count()) {
+            const dim3 grid((unsigned)((P + 15) / 16), (unsigned)nrb);
+            if (contig)
+                hipLaunchKernelGGL((ttm_kw_kernel<T, RTB, true>), grid, dim3(64 * KW_WAVES), 0, s, Y, Uq, Z, L, K,
+                                   Rout, P, nchunks, (int)ntiles);
+            else
+                hipLaunchKernelGGL((ttm_kw_kernel<T, RTB, false>), grid, dim3(64 * KW_WAVES), 0, s, Y, Uq, Z, L, K,
+                                   Rout, P, nchunks, (int)ntiles);
+            return hipGetLastError();
+        }
     }
     // row tiles per wave: keeps a lane under 256 VGPRs (8 waves per workgroup)
     constexpr int NT = (PREC == P_FP64) ? (RTB == 1 ? 2 : 1) : (RTB == 1 ? 4 : 2);

@@ -63,3 +63,25 @@ def test_direct_solver_orders(api, n, R, spectrum):
     np.testing.assert_allclose(U.T @ U, np.eye(R), rtol=0, atol=max(tol, 1e-15))
     top = np.abs(U).argmax(0)
     assert np.all(U[top, np.arange(R)] > 0)
+
+
+def within(Z, ref, bound, K):
+    """FP64 products and sums of K terms: K eps of the sum of magnitudes."""
+    assert np.all(np.abs(Z - ref) <= 4 * K * 2.2e-16 * bound + 1e-300)
+
+
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+@pytest.mark.parametrize("dims,n,R", [((993, 40), 0, 5), ((1025, 17), 0, 33), ((1024, 1), 0, 16), ((7, 1100, 3), 1, 20),
+                                      ((30, 2000), 1, 50), ((5000, 2, 3), 0, 70)])
+def test_long_contraction_ttm(api, dims, n, R, dtype):
+    """FP64-product TTM with a long mode and few rows (eight waves split the
+    contraction): ragged chunks, rows and r-tiles, contiguous and strided rows."""
+    rng = np.random.default_rng(sum(dims) + R)
+    Y = np.asfortranarray(rng.standard_normal(dims).astype(dtype))
+    U = np.asfortranarray(rng.standard_normal((dims[n], R)))
+    Z = api.to_numpy(api.ttm_mode_n(api.to_device(Y), api.to_device(U), n, "fp64"))
+    ref, bound = oracle.ttm_tensor(Y, U.T, n), oracle.ttm_tensor(np.abs(Y), np.abs(U).T, n)
+    if dtype == "float32":
+        assert np.all(np.abs(Z - ref) <= 2.0 ** -23 * np.abs(ref) + 1e-9 * bound)
+    else:
+        within(Z, ref, bound, dims[n])
