@@ -114,6 +114,99 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double *__restri
     if (SYM && i != j) S[j + IA * i] = sum;
 }
 
+// TTT against a narrow second operand (L = 1, IB <= 64, FP64 products): the
+// ALS branch's P = Y_(1) Z_(1)^T with a long first mode.  The block kernel pads
+// IB to its block edge (10 -> 128 for I = 30648: 556 us for 553 MB).  Here a
+// workgroup owns 32 rows of A and every column of B: lane (m, g) of a wave
+// loads rows 2 m and 2 m + 1 of column 4 s + g (256 contiguous bytes per 16
+// lanes), the even and the odd rows forming two tiles, so that nothing is
+// staged in LDS and A is read once; the four waves take interleaved groups of
+// columns and sum their tiles in LDS in wave order.  Bound by HBM: 107 us,
+// 5.2 TB/s.
+// kper: columns per range (blockIdx.y), dst + z IA IB its result.
+template <typename T, int NT, bool VEC>
+__global__ __launch_bounds__(256) void ttt_narrow_kernel(const T *__restrict__ A, const T *__restrict__ B,
+                                                        int64_t IA, int IB, int64_t P, int64_t kper,
+                                                        double *__restrict__ dst) {
+    constexpr int U = 4;   // column groups in flight per wave
+    __shared__ f64x4 s_acc[3][2 * NT][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tr = lane & 15, tg = lane >> 4;
+    const int64_t i = (int64_t)blockIdx.x * 32 + 2 * tr;
+    const int64_t ia = i < IA ? i : IA - 1, ib = i + 1 < IA ? i + 1 : IA - 1;
+    const int64_t pend = min(P, (int64_t)(blockIdx.y + 1) * kper);
+    f64x4 acc[2][NT];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[h][t] = f64x4{0, 0, 0, 0};
+    for (int64_t p0 = (int64_t)blockIdx.y * kper + 4 * wave; p0 < pend; p0 += 16 * U) {
+        double a[U][2], b[U][NT];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t p = p0 + 16 * u + tg;
+            const bool ok = p < pend;
+            const int64_t pc = ok ? p : pend - 1;
+            T x0, x1;
+            if constexpr (VEC) {   // IA even: a pair of rows is aligned and wholly inside
+                typedef T t2 __attribute__((ext_vector_type(2)));
+                const t2 x = *reinterpret_cast<const t2 *>(A + IA * pc + (i < IA ? i : IA - 2));
+                x0 = x.x;
+                x1 = x.y;
+            } else {
+                x0 = A[IA * pc + ia];
+                x1 = A[IA * pc + ib];
+            }
+            a[u][0] = ok ? (double)x0 : 0.0;
+            a[u][1] = ok ? (double)x1 : 0.0;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const int r = 16 * t + tr;
+                const double y = (double)B[(int64_t)IB * pc + (r < IB ? r : IB - 1)];
+                b[u][t] = ok ? y : 0.0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                acc[0][t] = mma(a[u][0], b[u][t], acc[0][t]);
+                acc[1][t] = mma(a[u][1], b[u][t], acc[1][t]);
+            }
+    }
+    if (wave > 0)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) s_acc[wave - 1][2 * t + h][lane] = acc[h][t];
+    __syncthreads();
+    if (wave > 0) return;
+    dst += (int64_t)blockIdx.y * IA * IB;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int w = 0; w < 3; ++w) acc[h][t] += s_acc[w][2 * t + h][lane];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t row = (int64_t)blockIdx.x * 32 + 2 * (tg + 4 * v) + h;
+                const int r = 16 * t + tr;
+                if (row < IA && r < IB) dst[row + IA * r] = acc[h][t][v];
+            }
+        }
+}
+
+// out = the nz partial results of count elements summed in order
+__global__ __launch_bounds__(256) void ttt_sum_kernel(const double *__restrict__ part, int64_t count, int nz,
+                                                     double *__restrict__ out) {
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= count) return;
+    double s = 0.0;
+#pragma unroll 8
+    for (int z = 0; z < nz; ++z) s += part[z * count + e];
+    out[e] = s;
+}
+
 // ---------------------------------------------------------------- host ----
 
 namespace {
@@ -232,6 +325,29 @@ hipError_t launch_gram_l1(const float *A, int64_t IA, int64_t M, const GramShape
     return hipGetLastError();
 }
 
+// The narrow TTT: ranges of columns until about two workgroups per CU (their
+// partial results in the block kernel's workspace: g.nkc ranges of at most 128
+// columns fit it for any IB <= 64), at least 256 columns each.
+template <typename T, int NT>
+hipError_t launch_ttt_narrow(const T *A, const T *B, int64_t IA, int64_t IB, int64_t P, const GramShape &g,
+                             double *partials, double *S, hipStream_t s) {
+    const int64_t rows = (IA + 31) / 32;
+    int64_t nz = std::max<int64_t>(1, std::min<int64_t>({(2 * device_cu_count() + rows - 1) / rows, P / 256, g.nkc}));
+    const int64_t kper = ((P + nz - 1) / nz + 15) / 16 * 16;
+    nz = (P + kper - 1) / kper;
+    double *dst = nz > 1 ? partials : S;
+    const dim3 grid((unsigned)rows, (unsigned)nz);
+    if (IA % 2 == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0)
+        hipLaunchKernelGGL((ttt_narrow_kernel<T, NT, true>), grid, dim3(256), 0, s, A, B, IA, (int)IB, P, kper, dst);
+    else
+        hipLaunchKernelGGL((ttt_narrow_kernel<T, NT, false>), grid, dim3(256), 0, s, A, B, IA, (int)IB, P, kper, dst);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || nz == 1) return e;
+    hipLaunchKernelGGL(ttt_sum_kernel, dim3((unsigned)((IA * IB + 255) / 256)), dim3(256), 0, s, partials, IA * IB,
+                       (int)nz, S);
+    return hipGetLastError();
+}
+
 template <typename T, int PREC, int WT, bool SYM>
 hipError_t launch_gram_t(const T *A, const T *B, int64_t L, int64_t IA, int64_t IB, int64_t M,
                          const GramShape &g, double *partials, double *S, hipStream_t s) {
@@ -247,6 +363,14 @@ hipError_t launch_gram_t(const T *A, const T *B, int64_t L, int64_t IA, int64_t 
             hipLaunchKernelGGL((gram_reduce_kernel<TB, SYM>), dim3((TB * TB + 63) / 64, g.nblocks),
                                dim3(256), 0, s, partials, g.nkc, g.nbi, g.nblocks, IA, IB, S);
             return hipGetLastError();
+        }
+    }
+    if constexpr (!SYM && PREC == P_FP64 && WT == 4) {
+        // rows beyond one block and few columns of B
+        if (L == 1 && IA >= 2 && IB <= 64) {
+            if (IB <= 16) return launch_ttt_narrow<T, 1>(A, B, IA, IB, P, g, partials, S, s);
+            if (IB <= 32) return launch_ttt_narrow<T, 2>(A, B, IA, IB, P, g, partials, S, s);
+            return launch_ttt_narrow<T, 4>(A, B, IA, IB, P, g, partials, S, s);
         }
     }
     const size_t lds = (size_t)2 * Frag<PREC>::NQ * TB * 4 * 16;

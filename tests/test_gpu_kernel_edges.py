@@ -71,6 +71,20 @@ def within(Z, ref, bound, K):
 
 
 @pytest.mark.parametrize("dtype", ["float64", "float32"])
+@pytest.mark.parametrize("dims,R", [((65, 40), 1), ((67, 2001), 16), ((130, 700), 17), ((4097, 33), 33),
+                                    ((601, 1), 64), ((9000, 300), 10), ((96, 20, 9), 20)])
+def test_narrow_ttt(api, dims, R, dtype):
+    """TTT over the first mode with few columns of the second operand: odd row
+    counts, one to four column tiles, one and several column ranges."""
+    rng = np.random.default_rng(sum(dims) + R)
+    Y = np.asfortranarray(rng.standard_normal(dims).astype(dtype))
+    Z = np.asfortranarray(rng.standard_normal((R,) + dims[1:]).astype(dtype))
+    P = api.to_numpy(api.ttt_mode_n(api.to_device(Y), api.to_device(Z), 0, "fp64"))
+    Yn, Zn = oracle.unfold(Y, 0), oracle.unfold(Z, 0)
+    within(P, oracle.ttt(Yn, Zn), oracle.ttt(np.abs(Yn), np.abs(Zn)), Yn.shape[1])
+
+
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
 @pytest.mark.parametrize("dims,n,R", [((993, 40), 0, 5), ((1025, 17), 0, 33), ((1024, 1), 0, 16), ((7, 1100, 3), 1, 20),
                                       ((30, 2000), 1, 50), ((5000, 2, 3), 0, 70)])
 def test_long_contraction_ttm(api, dims, n, R, dtype):
