@@ -175,7 +175,7 @@ static void plan_layout(sth_plan_s &pl) {
             maxUq = std::max(maxUq, std::max(ttm_prep_bytes(stp.I, stp.R, tp), ttm_prep_bytes(stp.R, stp.R, tp)));
             maxSmall = std::max(maxSmall, als_small_doubles(stp.I, stp.R) * sizeof(double));
             const int I = (int)stp.I, R = (int)stp.R;
-            maxGemm = std::max({maxGemm, gemm_ws_bytes(R, R, I), gemm_ws_bytes(I, R, R), gemm_ws_bytes(R, R, R)});
+            maxGemm = std::max(maxGemm, gemm_tn_ws_bytes(R, R, I));
         }
     }
     Arena a;
@@ -360,18 +360,18 @@ hipError_t cholqr3(const double *A, int I, int R, double *Q, double *Rfac, AlsBu
                    int64_t *flag, hipStream_t s) {
     hipError_t e;
     const double shift = 11.0 * ((double)I * R + (double)R * (R + 1)) * 1.1102230246251565e-16 * R;
-    if ((e = gemm_f64(1, 0, R, R, I, 1.0, A, I, A, I, 0.0, b.G2, R, gws, s))) return e;
+    if ((e = gemm_tn(R, R, I, A, I, A, I, b.G2, R, gws, s))) return e;
     if ((e = chol_launch(b.G2, R, R, shift, b.R1, b.R1inv, flag, s))) return e;
-    if ((e = gemm_f64(0, 0, I, R, R, 1.0, A, I, b.R1inv, R, 0.0, b.T1, I, gws, s))) return e;
-    if ((e = gemm_f64(1, 0, R, R, I, 1.0, b.T1, I, b.T1, I, 0.0, b.G2, R, gws, s))) return e;
+    if ((e = gemm_nn(false, I, R, R, A, I, b.R1inv, R, b.T1, I, s))) return e;
+    if ((e = gemm_tn(R, R, I, b.T1, I, b.T1, I, b.G2, R, gws, s))) return e;
     if ((e = chol_launch(b.G2, R, R, 0.0, b.R2, b.R2inv, flag, s))) return e;
-    if ((e = gemm_f64(0, 0, I, R, R, 1.0, b.T1, I, b.R2inv, R, 0.0, b.P, I, gws, s))) return e;
-    if ((e = gemm_f64(1, 0, R, R, I, 1.0, b.P, I, b.P, I, 0.0, b.G2, R, gws, s))) return e;
+    if ((e = gemm_nn(false, I, R, R, b.T1, I, b.R2inv, R, b.P, I, s))) return e;
+    if ((e = gemm_tn(R, R, I, b.P, I, b.P, I, b.G2, R, gws, s))) return e;
     if ((e = chol_launch(b.G2, R, R, 0.0, b.Rc, b.Rcinv, flag, s))) return e;
-    if ((e = gemm_f64(0, 0, I, R, R, 1.0, b.P, I, b.Rcinv, R, 0.0, Q, I, gws, s))) return e;
+    if ((e = gemm_nn(false, I, R, R, b.P, I, b.Rcinv, R, Q, I, s))) return e;
     if (Rfac) {
-        if ((e = gemm_f64(0, 0, R, R, R, 1.0, b.R2, R, b.R1, R, 0.0, b.C, R, gws, s))) return e;
-        if ((e = gemm_f64(0, 0, R, R, R, 1.0, b.Rc, R, b.C, R, 0.0, Rfac, R, gws, s))) return e;
+        if ((e = gemm_nn(false, R, R, R, b.R2, R, b.R1, R, b.C, R, s))) return e;
+        if ((e = gemm_nn(false, R, R, R, b.Rc, R, b.C, R, Rfac, R, s))) return e;
     }
     return hipSuccess;
 }
@@ -418,10 +418,10 @@ static sth_status exec_step(const sth_plan_s &pl, const Step &stp, const void *s
         // P = Y_(n) Z_(n)^T  (TTT)
         HIPCHK(gram_launch(p->dtype, gp, src, bufZ, stp.L, I, R, stp.M, false, part, b.P, s), "als ttt");
         // C = R_k^T R_k = Q^T P ;  L_{k+1} = P C^{-1}
-        HIPCHK(gemm_f64(1, 0, R, R, I, 1.0, b.Q, I, b.P, I, 0.0, b.C, R, gws, s), "als C");
+        HIPCHK(gemm_tn(R, R, I, b.Q, I, b.P, I, b.C, R, gws, s), "als C");
         HIPCHK(chol_launch(b.C, R, R, 0.0, b.Rc, b.Rcinv, flag, s), "als chol");
-        HIPCHK(gemm_f64(0, 0, I, R, R, 1.0, b.P, I, b.Rcinv, R, 0.0, b.T1, I, gws, s), "als L1");
-        HIPCHK(gemm_f64(0, 1, I, R, R, 1.0, b.T1, I, b.Rcinv, R, 0.0, b.Lk, I, gws, s), "als L2");
+        HIPCHK(gemm_nn(false, I, R, R, b.P, I, b.Rcinv, R, b.T1, I, s), "als L1");
+        HIPCHK(gemm_nn(true, I, R, R, b.T1, I, b.Rcinv, R, b.Lk, I, s), "als L2");
         const bool last = (k + 1 == p->als_iters);
         // next basis, or the final Q^ R^ = L
         HIPCHK(cholqr3(b.Lk, I, R, last ? Un : b.Q, last ? b.Rhat : nullptr, b, gws, flag, s), "als qr");

@@ -59,11 +59,12 @@ hipError_t teig_launch(const double *S, int64_t lds, int64_t n, int64_t R, doubl
                        int64_t *count, hipStream_t s);
 
 // Small FP64 LA and reductions (la.hip)
-int gemm_splits(int m, int n, int k);
-size_t gemm_ws_bytes(int m, int n, int k);
-hipError_t gemm_f64(int ta, int tb, int m, int n, int k, double alpha, const double *A,
-                    int64_t lda, const double *B, int64_t ldb, double beta, double *C, int64_t ldc,
-                    void *ws, hipStream_t s);
+// C = A^T B (m x n, contraction k; ws: gemm_tn_ws_bytes) and C = A op(B)
+size_t gemm_tn_ws_bytes(int m, int n, int k);
+hipError_t gemm_tn(int m, int n, int k, const double *A, int64_t lda, const double *B, int64_t ldb, double *C,
+                   int64_t ldc, void *ws, hipStream_t s);
+hipError_t gemm_nn(bool tb, int m, int n, int k, const double *A, int64_t lda, const double *B, int64_t ldb,
+                   double *C, int64_t ldc, hipStream_t s);
 // gate (may be null): run only when gate_open(gate, gate_R, gate_tol)
 hipError_t chol_launch(const double *G, int n, int64_t ldg, double shift_rel, double *R,
                        double *Rinv, int64_t *flag, hipStream_t s, const double *gate = nullptr,
