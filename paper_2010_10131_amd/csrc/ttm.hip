@@ -109,6 +109,22 @@ __global__ __launch_bounds__(256) void sum_pairs_kernel(const double *__restrict
     }
 }
 
+template <typename T, int PREC, int NCH, int WAVES, bool ERR>
+__global__ __launch_bounds__(64 * WAVES) void ttm_expand_kernel(
+    const T *__restrict__ Y, const uint4 *__restrict__ Uq, T *__restrict__ Z, int64_t L, int64_t K, int64_t Rout,
+    int64_t P, int nchunks, int ntiles, int rtn, int64_t nblocks, int64_t sa, int64_t sb,
+    const T *__restrict__ X, double *__restrict__ epart) {
+    ttm_expand_body<T, PREC, NCH, WAVES, ERR>(Y, Uq, Z, L, K, Rout, P, nchunks, ntiles, rtn, nblocks, sa, sb, X,
+                                              epart);
+}
+
+template <typename T, int PREC, int RTB, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void ttm_stream_kernel(
+    const T *__restrict__ Y, const uint4 *__restrict__ Uq, T *__restrict__ Z, int64_t L, int64_t K, int64_t Rout,
+    int64_t P, int nchunks, int ntiles, int64_t nblocks, int64_t sa, int64_t sb) {
+    ttm_stream_body<T, PREC, RTB, WAVES>(Y, Uq, Z, L, K, Rout, P, nchunks, ntiles, nblocks, sa, sb);
+}
+
 template <int PREC, int NT, int CPW, bool FULL>
 __global__ __launch_bounds__(64 * KS_WAVES) void ttm_ks_kernel(
     const float *__restrict__ Y, const uint4 *__restrict__ Uq, float *__restrict__ Z, int64_t K,
@@ -294,6 +310,107 @@ hipError_t launch_ttm_ks(const float *Y, const uint4 *Uq, float *Z, int64_t K, i
     return hipGetLastError();
 }
 
+// Strided rows in 16-byte vectors: L a multiple of the vector, aligned tensors.
+template <typename T>
+bool ttm_vec_ok(const void *Y, const void *Z, int64_t L) {
+    return L > 1 && L % (16 / (int64_t)sizeof(T)) == 0 &&
+           ((reinterpret_cast<uintptr_t>(Y) | reinterpret_cast<uintptr_t>(Z)) & 15) == 0;
+}
+
+// Grid of the vector kernels: row blocks of 16 V rows over the waves of at most
+// `cap` workgroups, and the (a, b) step from a wave's block to its next.
+template <typename T>
+struct VecGrid {
+    int64_t nblocks, wgs, sa, sb;
+    VecGrid(int64_t L, int64_t P, int waves, int64_t cap) {
+        constexpr int64_t V = 16 / sizeof(T);
+        nblocks = (P + 16 * V - 1) / (16 * V);
+        wgs = std::max<int64_t>(1, std::min<int64_t>((nblocks + waves - 1) / waves, cap));
+        const int64_t d = wgs * waves * 16 * V;
+        sb = d / L;
+        sa = d - sb * L;
+    }
+};
+
+// Chunks whose fragments the expansion kernel keeps in registers (0: too many)
+template <typename T, int PREC>
+constexpr int expand_chunks() { return PREC == P_FP64 && sizeof(T) == 4 ? 1 : 2; }
+
+// The expansion kernel (K <= 64): every r-tile from one read of Y where their
+// factor quads fit the LDS, equal ranges of r-tiles otherwise.
+template <typename T, int PREC, bool ERR>
+hipError_t launch_expand(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K, int64_t Rout, int64_t M,
+                         const T *X, double *part, int64_t *nparts, hipStream_t s) {
+    constexpr int NQ = Frag<PREC>::NQ;
+    const int64_t P = L * M;
+    const int nchunks = (int)((K + KC - 1) / KC), ntiles = (int)((Rout + 15) / 16);
+    // few row blocks: two waves a workgroup and ranges of r-tiles of at most 32
+    // KB, so that every CU has several workgroups (512^3 from 64^3, second
+    // expansion, 512 blocks: 31 -> 22 us)
+    const bool few = !ERR && P < (int64_t)16 * (16 / sizeof(T)) * TTM_WAVES * device_cu_count();
+    const int fit = (int)((few ? 32 * 1024 : TTM_LDS_MAX) / ((size_t)nchunks * NQ * 1024));
+    const int nrb = (ntiles + fit - 1) / fit, rtn = (ntiles + nrb - 1) / nrb;
+    const size_t lds = (size_t)nchunks * rtn * NQ * 1024;
+    const int64_t per_cu = lds <= 72 * 1024 ? 2 : 1;
+    const int waves = few ? 2 : TTM_WAVES;
+    const VecGrid<T> vg(L, P, waves, (int64_t)device_cu_count() * (few ? 4 : per_cu));
+    const dim3 grid((unsigned)vg.wgs, (unsigned)nrb);
+    auto go = [&](auto kern) -> hipError_t {
+        if (lds > 64 * 1024) {
+            hipError_t r = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (r != hipSuccess) return r;
+        }
+        hipLaunchKernelGGL(kern, grid, dim3(64 * waves), lds, s, Y, Uq, Z, L, K, Rout, P, nchunks, ntiles, rtn,
+                           vg.nblocks, vg.sa, vg.sb, X, part);
+        return hipGetLastError();
+    };
+    if (nparts) *nparts = vg.wgs * nrb;
+    if constexpr (!ERR) {
+        if (few) {
+            if constexpr (expand_chunks<T, PREC>() == 2) {
+                if (nchunks == 2) return go(ttm_expand_kernel<T, PREC, 2, 2, false>);
+            }
+            return go(ttm_expand_kernel<T, PREC, 1, 2, false>);
+        }
+    }
+    if constexpr (expand_chunks<T, PREC>() == 2) {
+        if (nchunks == 2) return go(ttm_expand_kernel<T, PREC, 2, TTM_WAVES, ERR>);
+    }
+    return go(ttm_expand_kernel<T, PREC, 1, TTM_WAVES, ERR>);
+}
+
+template <typename T, int PREC, int RTB, int WAVES>
+hipError_t launch_stream_w(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K, int64_t Rout, int64_t M,
+                           hipStream_t s) {
+    const int64_t P = L * M;
+    const int nchunks = (int)((K + KC - 1) / KC), ntiles = (int)((Rout + 15) / 16);
+    const size_t lds = (size_t)nchunks * RTB * Frag<PREC>::NQ * 1024;
+    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(16 / WAVES, (160 * 1024) / (int64_t)lds));
+    const VecGrid<T> vg(L, P, WAVES, (int64_t)device_cu_count() * per_cu);
+    auto kern = ttm_stream_kernel<T, PREC, RTB, WAVES>;
+    if (lds > 64 * 1024) {
+        hipError_t r = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (r != hipSuccess) return r;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)vg.wgs, (unsigned)((ntiles + RTB - 1) / RTB)), dim3(64 * WAVES), lds,
+                       s, Y, Uq, Z, L, K, Rout, P, nchunks, ntiles, vg.nblocks, vg.sa, vg.sb);
+    return hipGetLastError();
+}
+
+// The streaming kernel.  Where its row blocks give every CU eight waves, all
+// RTB r-tiles of a block stay together and Y is read once; with fewer blocks the
+// r-tiles are spread over workgroups of fewer waves (Y, then a few tens of MB at
+// most, is read again from the caches): 512^3 modes 2 and 3 (512 and 64 blocks)
+// took 59 us together in workgroups of eight waves and four r-tiles.
+template <typename T, int PREC, int RTB>
+hipError_t launch_stream(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K, int64_t Rout, int64_t M,
+                         hipStream_t s) {
+    const int64_t nblocks = (L * M + 16 * (16 / sizeof(T)) - 1) / (16 * (16 / sizeof(T))), cu = device_cu_count();
+    if (nblocks >= 8 * cu) return launch_stream_w<T, PREC, RTB, 8>(Y, Uq, Z, L, K, Rout, M, s);
+    if (nblocks >= cu) return launch_stream_w<T, PREC, (RTB < 2 ? RTB : 2), 4>(Y, Uq, Z, L, K, Rout, M, s);
+    return launch_stream_w<T, PREC, 1, 2>(Y, Uq, Z, L, K, Rout, M, s);
+}
+
 template <typename T, int PREC, int RTB>
 hipError_t launch_ttm_r(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K, int64_t Rout,
                         int64_t M, hipStream_t s) {
@@ -324,6 +441,14 @@ hipError_t launch_ttm_r(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K,
                 hipLaunchKernelGGL((ttm_kw_kernel<T, RTB, false>), grid, dim3(64 * KW_WAVES), 0, s, Y, Uq, Z, L, K,
                                    Rout, P, nchunks, (int)ntiles);
             return hipGetLastError();
+        }
+    }
+    if (ttm_vec_ok<T>(Y, Z, L)) {
+        if (nchunks <= expand_chunks<T, PREC>())
+            return launch_expand<T, PREC, false>(Y, Uq, Z, L, K, Rout, M, nullptr, nullptr, nullptr, s);
+        // FP64 accumulators of four tiles x four rows do not fit the registers
+        if constexpr (!(PREC == P_FP64 && sizeof(T) == 4 && RTB == 4)) {
+            if (lds <= TTM_LDS_MAX) return launch_stream<T, PREC, RTB>(Y, Uq, Z, L, K, Rout, M, s);
         }
     }
     // row tiles per wave: keeps a lane under 256 VGPRs (8 waves per workgroup)
@@ -393,6 +518,17 @@ hipError_t launch_ttm_err_r(const T *Y, const uint4 *Uq, const T *X, int64_t L, 
 template <typename T, int PREC>
 hipError_t launch_ttm_err_p(const T *Y, const uint4 *Uq, const T *X, int64_t L, int64_t K, int64_t Rout,
                             int64_t M, double *part, double *out, hipStream_t s) {
+    const int64_t nchunks = (K + KC - 1) / KC;
+    // the expansion kernel's workgroups (at most two per CU and r-range) fit the
+    // partial sums' buffer where the factor fits the LDS in one range
+    if (ttm_vec_ok<T>(Y, X, L) && nchunks <= expand_chunks<T, PREC>() &&
+        (size_t)nchunks * ((Rout + 15) / 16) * Frag<PREC>::NQ * 1024 <= TTM_LDS_MAX) {
+        int64_t np = 0;
+        hipError_t e = launch_expand<T, PREC, true>(Y, Uq, nullptr, L, K, Rout, M, X, part, &np, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(sum_pairs_kernel, dim3(1), dim3(256), 0, s, part, np, out);
+        return hipGetLastError();
+    }
     switch (ttm_err_rtb(Rout)) {
         case 1: return launch_ttm_err_r<T, PREC, 1>(Y, Uq, X, L, K, Rout, M, part, out, s);
         case 2: return launch_ttm_err_r<T, PREC, 2>(Y, Uq, X, L, K, Rout, M, part, out, s);

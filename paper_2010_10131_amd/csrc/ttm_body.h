@@ -442,4 +442,277 @@ __device__ __forceinline__ void ttm_ks_body(const float *__restrict__ Y, const u
     }
 }
 
+// ---------------------------------------------------------------------------
+// TTM for strided rows (L > 1) with L a multiple of V = 16 / sizeof(T): 16 V
+// consecutive rows per wave, row p0 + V m + q being row m of tile q, so that
+// the V tiles of a lane are V consecutive values: every load of Y and every
+// store of Z is 16 bytes per lane, 256 contiguous bytes per 16 lanes (4 bytes
+// and 64 in the general kernel).  The sums are the general kernel's, in its
+// order: the same bits.  Bound by HBM: 64 -> 512 over 262144 rows (bf16x3, 604
+// MB) 200 -> 113 us, 5.35 TB/s; the error sums over 48^5 (8 -> 48, FP32, 1.19 GB)
+// 960 -> 291 us.
+
+// (row index a, outer index b) of a lane's first row, stepped without a
+// division: a block further on is (step_a, step_b) away.
+struct TtmRow {
+    int64_t a, b;
+    __device__ __forceinline__ void init(int64_t p, int64_t L) {
+        b = p / L;
+        a = p - b * L;
+    }
+    __device__ __forceinline__ void step(int64_t sa, int64_t sb, int64_t L) {
+        a += sa;
+        b += sb;
+        if (a >= L) {
+            a -= L;
+            ++b;
+        }
+    }
+};
+
+template <typename T> struct TtmVec;
+template <> struct TtmVec<float> {
+    typedef float type __attribute__((ext_vector_type(4)));
+};
+template <> struct TtmVec<double> {
+    typedef double type __attribute__((ext_vector_type(2)));
+};
+
+// rows 8 g .. 8 g + 7 (of chunk c) of a lane's V columns; zero past K
+template <typename T>
+__device__ __forceinline__ void ttm_load_vec(const T *__restrict__ y, int64_t L, int64_t K, int c, int g,
+                                             typename TtmVec<T>::type (&x)[8]) {
+    typedef typename TtmVec<T>::type V;
+    const int64_t kb = (int64_t)c * KC + 8 * g;
+    if ((int64_t)(c + 1) * KC <= K) {   // uniform
+        const T *src = y + L * kb;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = *reinterpret_cast<const V *>(src + L * j);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int64_t k = kb + j;
+            V v = {};
+            if (k < K) v = *reinterpret_cast<const V *>(y + L * k);
+            x[j] = v;
+        }
+    }
+}
+
+// K <= 32 NCH: the rows' fragments for the whole contraction stay in registers
+// and the r-tiles rt0 .. rt0 + rtn - 1 of the factor pass by from LDS, so Y is
+// read once whatever Rout is (a reconstruction's expansions, 64 -> 512: the
+// general kernel read Y once per 64 outputs) and one tile's accumulators are
+// live.  The next block's rows load while this one is multiplied.  ERR: see
+// ttm_body; the values of X for the next r-tile load ahead of it.
+template <typename T, int PREC, int NCH, int WAVES, bool ERR>
+__device__ __forceinline__ void ttm_expand_body(const T *__restrict__ Y, const uint4 *__restrict__ Uq,
+                                                T *__restrict__ Z, int64_t L, int64_t K, int64_t Rout, int64_t P,
+                                                int nchunks, int ntiles, int rtn, int64_t nblocks, int64_t sa,
+                                                int64_t sb, const T *__restrict__ Xe, double *__restrict__ epart) {
+    constexpr int NQ = Frag<PREC>::NQ, V = 16 / sizeof(T);
+    typedef typename Acc<PREC>::type AccT;
+    typedef typename TtmVec<T>::type VT;
+    extern __shared__ uint4 s_u[];   // [c][rt][q][lane]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
+    const int rt0 = blockIdx.y * rtn;
+    const int nrt = min(rtn, ntiles - rt0);
+    const int per_chunk = nrt * NQ * 64;
+    for (int e = threadIdx.x; e < nchunks * per_chunk; e += 64 * WAVES) {
+        const int c = e / per_chunk;
+        s_u[e] = Uq[((int64_t)c * ntiles + rt0) * NQ * 64 + (e - c * per_chunk)];
+    }
+    __syncthreads();
+
+    double esq_d = 0.0, esq_x = 0.0;
+    const int64_t wstride = (int64_t)gridDim.x * WAVES;
+    int64_t wb = (int64_t)blockIdx.x * WAVES + wave;
+    TtmRow row;
+    VT raw[NCH][8];
+    auto fetch = [&](int64_t blk) {
+        // a lane past the last row reads the last block's first rows
+        const int64_t p = blk * (16 * V) + V * (lane & 15);
+        const T *y = p < P ? Y + row.a + L * K * row.b : Y;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+            if (c < nchunks) ttm_load_vec<T>(y, L, K, c, g, raw[c]);
+    };
+    if (wb < nblocks) {
+        row.init(wb * (16 * V) + V * (lane & 15), L);
+        fetch(wb);
+    }
+    for (; wb < nblocks; wb += wstride) {
+        Frag<PREC> yb[NCH][V];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+            if (c < nchunks)
+#pragma unroll
+                for (int q = 0; q < V; ++q) {
+                    T x[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) x[j] = raw[c][j][q];
+                    make_frag(x, yb[c][q]);
+                }
+        const bool valid = wb * (16 * V) + V * (lane & 15) < P;
+        const int64_t zoff = valid ? row.a + L * Rout * row.b : 0;
+        if (wb + wstride < nblocks) {
+            row.step(sa, sb, L);
+            fetch(wb + wstride);
+        }
+        VT xe[2][4];
+        auto fetch_x = [&](int rt, VT (&x)[4]) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t r = (int64_t)(rt0 + rt) * 16 + drow<PREC>(g, v);
+                x[v] = *reinterpret_cast<const VT *>(Xe + zoff + L * (r < Rout ? r : Rout - 1));
+            }
+        };
+        auto tile = [&](int rt, VT (&x)[4]) {
+            AccT acc[V];
+#pragma unroll
+            for (int q = 0; q < V; ++q) acc[q] = AccT{0, 0, 0, 0};
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+                if (c < nchunks) {
+                    FragQ<PREC> ua;
+                    const uint4 *src = s_u + (c * nrt + rt) * NQ * 64 + lane;
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) ua.q[q] = src[q * 64];
+#pragma unroll
+                    for (int q = 0; q < V; ++q) mma_frag(ua.f, yb[c][q], acc[q]);
+                }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t r = (int64_t)(rt0 + rt) * 16 + drow<PREC>(g, v);
+                const bool ok = valid && r < Rout;
+                if constexpr (ERR) {
+#pragma unroll
+                    for (int q = 0; q < V; ++q) {
+                        const double xv = ok ? (double)x[v][q] : 0.0;
+                        const double d = ok ? xv - (double)(T)acc[q][v] : 0.0;
+                        esq_d += d * d;
+                        esq_x += xv * xv;
+                    }
+                } else {
+                    VT z;
+#pragma unroll
+                    for (int q = 0; q < V; ++q) z[q] = (T)acc[q][v];
+                    if (ok) *reinterpret_cast<VT *>(Z + zoff + L * r) = z;
+                }
+            }
+        };
+        if constexpr (ERR) {
+            fetch_x(0, xe[0]);
+            for (int rt = 0; rt < nrt; rt += 2) {
+                if (rt + 1 < nrt) fetch_x(rt + 1, xe[1]);
+                tile(rt, xe[0]);
+                if (rt + 1 < nrt) {
+                    if (rt + 2 < nrt) fetch_x(rt + 2, xe[0]);
+                    tile(rt + 1, xe[1]);
+                }
+            }
+        } else {
+            for (int rt = 0; rt < nrt; ++rt) tile(rt, xe[0]);
+        }
+    }
+    if constexpr (ERR) {
+        // fixed-order workgroup sums: lanes by xor shuffles, then waves in order
+        __shared__ double s_err[2][WAVES];
+        for (int o = 32; o > 0; o >>= 1) {
+            esq_d += __shfl_xor(esq_d, o);
+            esq_x += __shfl_xor(esq_x, o);
+        }
+        if (lane == 0) {
+            s_err[0][wave] = esq_d;
+            s_err[1][wave] = esq_x;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double a = 0.0, b = 0.0;
+            for (int w = 0; w < WAVES; ++w) {
+                a += s_err[0][w];
+                b += s_err[1][w];
+            }
+            const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+            epart[2 * id] = a;
+            epart[2 * id + 1] = b;
+        }
+    }
+}
+
+// Longer contractions: the chunks stream by, the accumulators of RTB r-tiles
+// stay in registers, the next chunk (of this block or of the next) in flight.
+template <typename T, int PREC, int RTB, int WAVES>
+__device__ __forceinline__ void ttm_stream_body(const T *__restrict__ Y, const uint4 *__restrict__ Uq,
+                                                T *__restrict__ Z, int64_t L, int64_t K, int64_t Rout, int64_t P,
+                                                int nchunks, int ntiles, int64_t nblocks, int64_t sa, int64_t sb) {
+    constexpr int NQ = Frag<PREC>::NQ, V = 16 / sizeof(T);
+    typedef typename Acc<PREC>::type AccT;
+    typedef typename TtmVec<T>::type VT;
+    extern __shared__ uint4 s_u[];   // [c][rt][q][lane]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
+    const int rt0 = blockIdx.y * RTB, nrt = min(RTB, ntiles - rt0);
+    constexpr int per_chunk = RTB * NQ * 64;
+    for (int e = threadIdx.x; e < nchunks * per_chunk; e += 64 * WAVES) {
+        const int c = e / per_chunk, rem = e - c * per_chunk;
+        s_u[e] = rem / (NQ * 64) < nrt ? Uq[((int64_t)c * ntiles + rt0) * NQ * 64 + rem] : make_uint4(0, 0, 0, 0);
+    }
+    __syncthreads();
+
+    const int64_t wstride = (int64_t)gridDim.x * WAVES;
+    int64_t wb = (int64_t)blockIdx.x * WAVES + wave;
+    if (wb >= nblocks) return;
+    TtmRow row;
+    row.init(wb * (16 * V) + V * (lane & 15), L);
+    const T *y = wb * (16 * V) + V * (lane & 15) < P ? Y + row.a + L * K * row.b : Y;
+    VT raw[8];
+    ttm_load_vec<T>(y, L, K, 0, g, raw);
+    for (; wb < nblocks; wb += wstride) {
+        const bool valid = wb * (16 * V) + V * (lane & 15) < P;
+        const int64_t zoff = row.a + L * Rout * row.b;
+        AccT acc[V][RTB];
+#pragma unroll
+        for (int q = 0; q < V; ++q)
+#pragma unroll
+            for (int rt = 0; rt < RTB; ++rt) acc[q][rt] = AccT{0, 0, 0, 0};
+        for (int c = 0; c < nchunks; ++c) {
+            Frag<PREC> yb[V];
+#pragma unroll
+            for (int q = 0; q < V; ++q) {
+                T x[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) x[j] = raw[j][q];
+                make_frag(x, yb[q]);
+            }
+            if (c + 1 < nchunks) {
+                ttm_load_vec<T>(y, L, K, c + 1, g, raw);
+            } else if (wb + wstride < nblocks) {
+                row.step(sa, sb, L);
+                y = (wb + wstride) * (16 * V) + V * (lane & 15) < P ? Y + row.a + L * K * row.b : Y;
+                ttm_load_vec<T>(y, L, K, 0, g, raw);
+            }
+#pragma unroll
+            for (int rt = 0; rt < RTB; ++rt) {
+                FragQ<PREC> ua;
+                const uint4 *src = s_u + (c * RTB + rt) * NQ * 64 + lane;
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) ua.q[q] = src[q * 64];
+#pragma unroll
+                for (int q = 0; q < V; ++q) mma_frag(ua.f, yb[q], acc[q][rt]);
+            }
+        }
+        if (valid)
+#pragma unroll
+            for (int rt = 0; rt < RTB; ++rt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int64_t r = (int64_t)(rt0 + rt) * 16 + drow<PREC>(g, v);
+                    VT z;
+#pragma unroll
+                    for (int q = 0; q < V; ++q) z[q] = (T)acc[q][rt][v];
+                    if (r < Rout) *reinterpret_cast<VT *>(Z + zoff + L * r) = z;
+                }
+    }
+}
+
 }  // namespace sth

@@ -99,3 +99,41 @@ def test_long_contraction_ttm(api, dims, n, R, dtype):
         assert np.all(np.abs(Z - ref) <= 2.0 ** -23 * np.abs(ref) + 1e-9 * bound)
     else:
         within(Z, ref, bound, dims[n])
+
+
+@pytest.mark.parametrize("prec", ["f64", "fp64", "fp32", "bf16x3", "bf16x6"])
+@pytest.mark.parametrize("dims,n,R", [((4, 8, 1), 1, 1), ((4, 3, 5), 1, 17), ((12, 32, 7), 1, 48), ((20, 33, 9), 1, 200),
+                                      ((64, 64, 3), 1, 16), ((8, 65, 11), 1, 5), ((132, 97, 2), 1, 33),
+                                      ((16, 300, 5), 1, 64), ((4, 20, 6), 2, 700), ((6, 40, 5), 1, 10)])
+def test_strided_ttm_in_vectors(api, dims, n, R, prec):
+    """Strided rows in 16-byte vectors (L a multiple of 4 values, or of 2 in
+    FP64): last blocks that are not whole, contractions of one chunk, of two and
+    beyond, r-tiles in one range and in several.  FP32 sums of K products (FP64
+    ones: K eps), rounded to the data type."""
+    dtype = "float64" if prec == "f64" else "float32"
+    rng = np.random.default_rng(sum(dims) + R)
+    Y = np.asfortranarray(rng.standard_normal(dims).astype(dtype))
+    U = np.asfortranarray(rng.standard_normal((dims[n], R)))
+    Z = api.to_numpy(api.ttm_mode_n(api.to_device(Y), api.to_device(U), n, "fp64" if prec == "f64" else prec))
+    ref, bound = oracle.ttm_tensor(Y, U.T, n), oracle.ttm_tensor(np.abs(Y), np.abs(U).T, n)
+    K = dims[n]
+    unit = {"f64": 4 * K * 2.2e-16, "fp64": 2.0 ** -23, "fp32": (K + 2) * 2.0 ** -23,
+            "bf16x3": (K + 2) * 2.0 ** -23 + 2.0 ** -15, "bf16x6": (K + 6) * 2.0 ** -23}[prec]
+    assert np.all(np.abs(Z - ref) <= unit * bound + 1e-30)
+
+
+@pytest.mark.parametrize("dims,ranks", [((20, 12, 9), (5, 6, 4)), ((8, 10, 37), (3, 5, 33)), ((36, 9, 50), (4, 3, 40))])
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+def test_error_sums_in_vectors(api, dims, ranks, dtype):
+    """The fused error sums on tensors whose last mode has strided rows in whole
+    vectors, against the oracle's reconstruction; the squares of differences of
+    order one are summed in FP64."""
+    rng = np.random.default_rng(sum(dims))
+    G = np.asfortranarray(rng.standard_normal(ranks).astype(dtype))
+    U = [np.asfortranarray(np.linalg.qr(rng.standard_normal((d, r)))[0]) for d, r in zip(dims, ranks)]
+    X = np.asfortranarray(rng.standard_normal(dims).astype(dtype))
+    out = api.tucker_error(api.to_device(X), api.to_device(G), [api.to_device(u) for u in U],
+                           "fp64" if dtype == "float64" else "fp32").cpu().numpy()
+    Xo = oracle.reconstruct(G.astype(np.float64), U)
+    tol = 1e-12 if dtype == "float64" else 1e-5
+    np.testing.assert_allclose(out, [np.sum((X - Xo) ** 2), np.sum(X.astype(np.float64) ** 2)], rtol=tol)
