@@ -3,6 +3,7 @@
 // iteration eigensolver, and by the batched eigensolver).
 #pragma once
 #include "common.h"
+#include <type_traits>
 
 namespace sth {
 
@@ -12,41 +13,117 @@ namespace sth {
 // G (n x n, symmetric, ldg) + shift_rel * trace(G) / n * I = L L^T.  The
 // matrix is padded with an identity block to np = 16 * ceil(n / 16), so that
 // every block is a full 16 x 16 tile (the padded factor is diag(L, I)).
-// Blocked right-looking Cholesky with 16-column panels:
-//   * the diagonal block is factored by one wave in registers (row l of the
-//     block in lane l, right-looking within the block, columns broadcast with
-//     lane reads, 1 / sqrt from the reciprocal square root), and the same
-//     wave inverts it (lane c solves for column c of D^{-1} = L(K, K)^{-1});
-//     D^{-1} is kept, transposed, in the unused upper half of the block;
-//   * the panel below it is P = A(B, K) D^{-T}, one 16 x 16 x 16 product per
-//     row tile on the FP64 matrix cores;
-//   * the trailing matrix gets the rank-16 update A(bi, bj) -= P(bi) P(bj)^T
-//     on the matrix cores (16 x 16 tiles of the lower triangle).
-// L is then inverted in place block column by block column from the last
-// one:  L^{-1}(B, K) = -(sum_{J in (K, B]} L^{-1}(B, J) L(J, K)) D_K^{-1},
-// both products on the matrix cores, D_K^{-1} the kept inverse.
-// Writes R = L^T (upper, may be NULL) and Rinv = L^{-T} (upper), n x n.  A
-// non-positive pivot sets flag[0] = 2 and is replaced by a tiny positive one
-// so that the run continues.
+// Right-looking on the augmented matrix [A | I] in 16-column panels, so that
+// row block K of L^{-1} is final with panel K.  Per panel:
+//   * diagonal block: one wave factors it and inverts it in one stream of
+//     instructions.  Row l of the block is in lane l of the even 16-lane rows,
+//     column l of D^{-1} in lane l of the odd ones: both take the step
+//     a_c -= L(c, J) a_J, with column J of L as an FP64 DPP operand;
+//   * panel: P(B) = A(B, K) D^{-T} below it (kept in its own buffer) and
+//     L^{-1}(K, J) = D^{-1} W(K, J) left of it, nb - 1 products of 16 x 16 tiles
+//     on the FP64 matrix cores;
+//   * trailing update A(B, C) -= P(B) P(C)^T and W(B, J) -= P(B) L^{-1}(K, J) on
+//     the matrix cores.  W(B, J) (J <= K) lies where L(B, J) was.  The first wave
+//     updates the next diagonal block and goes on to factor it while the others
+//     do the rest: two barriers per panel.
+// Writes R = L^T (upper, may be NULL) and Rinv = L^{-T} (upper), n x n, tile by
+// tile as they become final.  A non-positive pivot sets flag[0] = 2 and is
+// replaced by a tiny positive one so that the run continues.
 //
-// L lives in LDS with an odd leading dimension (np + 1), so that walking a
-// row and walking a column are both free of bank conflicts.
+// Bound by the serial chain of the diagonal blocks.  Against the form with lane
+// reads for the broadcasts, the library's rsqrt, the inversion of L as a second
+// sweep and five barriers per panel, order 16 went from 9.6 to 5.6 us, order 80
+// from 43 to 15 us, order 128 from 75 to 25 us.
+//
+// L lives in LDS with an odd leading dimension, so that walking a row and
+// walking a column are both free of bank conflicts; a constant one, so that every
+// offset within a tile is an immediate (a lone wave is bound by its instructions).
 constexpr int CB = 16;
+constexpr int CLD = 129;
 
 __host__ __device__ inline int chol_np(int64_t n) { return (int)((n + CB - 1) / CB * CB); }
-__host__ __device__ inline int chol_ld(int64_t n) { return chol_np(n) + 1; }
 
-// Dynamic LDS of chol_body: L (np x ld), the product buffer (np x CB) and the
-// reciprocals of the diagonal of L (np).
+// Dynamic LDS of chol_body: L (CLD x np) and the panel P (CLD x CB).
 __host__ __device__ inline size_t chol_lds_bytes(int64_t n) {
-    return (size_t)(chol_np(n) * chol_ld(n) + chol_np(n) * CB + chol_np(n)) * 8;
+    return (size_t)CLD * (chol_np(n) + CB) * 8;
 }
 
-// value of v in lane `src` (src uniform across the wave)
-__device__ __forceinline__ double lane_value(double v, int src) {
+// v of lane `src` of the wave (uniform)
+__device__ __forceinline__ double chol_lane(double v, int src) {
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
     const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
     return __hiloint2double(hi, lo);
+}
+// Every lane: v of the lane of the even 16-lane row of its pair of rows.
+__device__ __forceinline__ double chol_even_row(double v) {
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __hiloint2double((int)b[0], (int)a[0]);
+}
+// a_c -= src(lane N + c of each 16-lane row) * m, c < 4 (FP64 DPP broadcast; the
+// s_nop keeps the two wait states a DPP read needs after a VALU write)
+template <int N>
+__device__ __forceinline__ void chol_bc4(double &a0, double &a1, double &a2, double &a3, double src, double m) {
+    asm("s_nop 1\n"
+        "v_fmac_f64_dpp %0, -%4, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %1, -%4, %5 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %2, -%4, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %3, -%4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+        : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3)
+        : "v"(src), "v"(m), "n"(N), "n"(N + 1), "n"(N + 2), "n"(N + 3));
+}
+template <int N>
+__device__ __forceinline__ void chol_bc1(double &a, double src, double m) {
+    asm("s_nop 1\n v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+        : "+v"(a)
+        : "v"(src), "v"(m), "n"(N));
+}
+// a[c] -= src(lane c) * m for c = C .. 15
+template <int C>
+__device__ __forceinline__ void chol_bc(double (&a)[CB], double src, double m) {
+    if constexpr (C < CB) {
+        if constexpr (C % 4 == 0) {
+            chol_bc4<C>(a[C], a[C + 1], a[C + 2], a[C + 3], src, m);
+            chol_bc<C + 4>(a, src, m);
+        } else {
+            chol_bc1<C>(a[C], src, m);
+            chol_bc<C + 1>(a, src, m);
+        }
+    }
+}
+
+// Column steps J.. of a 16 x 16 block: a is row l of the block (even 16-lane
+// rows, piv = l) or column l of its factor's inverse, begun as e_l (odd rows,
+// piv < 0).  REPAIR replaces non-positive pivots by tiny; without it bad only
+// tells that there was one.
+template <bool REPAIR, int J>
+__device__ __forceinline__ void chol_block(double (&a)[CB], int piv, double tiny, bool &bad) {
+    if constexpr (J < CB) {
+        double d = chol_lane(a[J], J);
+        const bool neg = !(d > 0.0);
+        bad |= neg;
+        if constexpr (REPAIR) {
+            d = neg ? tiny : d;
+            if (piv == J) a[J] = d;
+        }
+        const double col = chol_even_row(a[J]);
+        // 1 / sqrt(d): the hardware estimate with one third-order step
+        double rd = __builtin_amdgcn_rsq(d);
+        const double e = fma(-d * rd, rd, 1.0);
+        rd = fma(rd * e, fma(0.375, e, 0.5), rd);
+        a[J] *= rd;
+        chol_bc<J + 1>(a, col * rd, a[J]);
+        chol_block<REPAIR, J + 1>(a, piv, tiny, bad);
+    }
+}
+
+// Barrier that orders LDS only: the stores of finished tiles to global memory
+// stay in flight across it (nothing here reads them back).
+__device__ __forceinline__ void chol_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 template <int NTH>
@@ -54,189 +131,166 @@ __device__ __forceinline__ void chol_body(const double *__restrict__ G, int n, i
                                           double shift_rel, double *__restrict__ Rout,
                                           double *__restrict__ Rinv, int64_t *__restrict__ flag) {
     constexpr int NW = NTH / 64;
-    constexpr int LC = 8;   // columns per wave and load step (16 loads in flight per thread)
+    constexpr int LC = 128 / NW;   // columns per wave at most
     extern __shared__ __align__(16) double s_l[];  // L, column-major, leading dimension ld
-    const int np = chol_np(n), ld = np + 1, nb = np / CB;
-    double *s_tmp = s_l + np * ld;   // np x CB
-    double *s_rd = s_tmp + np * CB;  // 1 / L(i, i)
-    __shared__ double s_dinv[CB * CB];
-    __shared__ double s_tr;
+    const int np = chol_np(n), nb = np / CB;
+    double *s_p = s_l + np * CLD;   // panel P
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tr = lane & 15, tg = lane >> 4;   // matrix-core tile coordinates
+    const int rc = tr + CLD * tg;   // element (row tr, column tg) of a tile
+    const int cr = tg + CLD * tr;   // element (row tg, column tr)
 
-    // lower triangle of G padded with the identity
-    for (int j0 = LC * wave; j0 < np; j0 += LC * NW) {
+    // lower triangle of G padded with the identity: every load issued before the
+    // first is stored
+    {
         double v[LC][2];
 #pragma unroll
         for (int u = 0; u < LC; ++u)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const int j = j0 + u, i = lane + 64 * h;
-                double x = 0.0;
-                if (j < n && i < n) x = (i >= j) ? G[i + ldg * j] : 0.0;
-                else if (i == j) x = 1.0;
-                v[u][h] = x;
+                const int j = wave + NW * u, i = lane + 64 * h;
+                v[u][h] = i == j ? 1.0 : 0.0;
+                if (64 * h < n && j < n && i < n && i >= j) v[u][h] = G[i + ldg * j];
             }
 #pragma unroll
         for (int u = 0; u < LC; ++u)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const int j = j0 + u, i = lane + 64 * h;
-                if (j < np && i < np) s_l[i + ld * j] = v[u][h];
+                const int j = wave + NW * u, i = lane + 64 * h;
+                if (j < np && i < np) s_l[i + CLD * j] = v[u][h];
             }
     }
     __syncthreads();
+    double tiny = 0.0;
+    bool bad = false;
+    // a 16 x 16 identity beside the first diagonal block (the panel's place when
+    // that is the only block): the odd rows' start of every block
+    const int ident = CLD * CB;
     if (wave == 0) {
         double t = 0.0;
-        for (int i = lane; i < n; i += 64) t += s_l[i + ld * i];
+        for (int i = lane; i < n; i += 64) t += s_l[i + CLD * i];
         for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
-        if (lane == 0) s_tr = t;
+        if (shift_rel != 0.0)
+            for (int i = lane; i < n; i += 64) s_l[i + CLD * i] += shift_rel * t / n;
+        tiny = 1e-300 + 1e-30 * fabs(t);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s_l[ident + cr + 4 * v] = tg + 4 * v == tr ? 1.0 : 0.0;
+    } else {
+        // the triangles outside R and Rinv, but for the diagonal blocks
+        for (int j = wave - 1; j < n; j += NW - 1)
+            for (int i = (j / CB + 1) * CB + lane; i < n; i += 64) {
+                if (Rout) Rout[i + n * j] = 0.0;
+                Rinv[i + n * j] = 0.0;
+            }
     }
-    __syncthreads();
-    if (shift_rel != 0.0) {
-        const double sh = shift_rel * s_tr / n;
-        for (int i = tid; i < n; i += NTH) s_l[i + ld * i] += sh;
-        __syncthreads();
-    }
-    const double tiny = 1e-300 + 1e-30 * fabs(s_tr);
-    bool bad = false;
+    // tile c -= P(b) X (c begun as 0 where fresh): X(k, j) = x[XK k + XJ j]
+    auto update = [&](int b, double *c, bool fresh, const double *x, auto xt) {
+        constexpr bool XT = decltype(xt)::value;
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+        if (!fresh)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[v] = c[cr + 4 * v];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-s_p[CB * b + rc + 4 * kk * CLD],
+                                                       XT ? x[rc + 4 * kk * CLD] : x[cr + 4 * kk], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) c[cr + 4 * v] = acc[v];
+    };
+    // acc = D^{-1} X with D^{-1} in the diagonal block dk
+    auto solve = [&](const double *dk, const double *x, auto xt) {
+        constexpr bool XT = decltype(xt)::value;
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(dk[rc + 4 * kk * CLD], XT ? x[rc + 4 * kk * CLD] : x[cr + 4 * kk],
+                                                       acc, 0, 0, 0);
+        return acc;
+    };
+    using TransX = std::true_type;
+    using PlainX = std::false_type;
     for (int kb = 0; kb < nb; ++kb) {
-        const int k0 = kb * CB, t0 = k0 + CB;
-        // 1. diagonal block: wave 0, row l of the block in lane l
+        const int k0 = kb * CB, kp = kb - 1;
+        double *dk = s_l + k0 + CLD * k0;
         if (wave == 0) {
-            double row[CB];
-            double myrd = 0.0;
+            // the diagonal block, with the previous panel's update
+            if (kb) update(kb, dk, false, s_p + k0, TransX());
+            const bool even = (tg & 1) == 0;
+            const double *src = even ? dk : s_l + ident;
+            double a[CB];
 #pragma unroll
-            for (int c = 0; c < CB; ++c) row[c] = (lane < CB) ? s_l[k0 + lane + ld * (k0 + c)] : 0.0;
+            for (int c = 0; c < CB; ++c) a[c] = src[tr + CLD * c];
+            bool neg = false;
+            chol_block<false, 0>(a, tr, tiny, neg);
+            if (neg) {   // repeated with the pivots replaced
+                bad = true;
 #pragma unroll
-            for (int j = 0; j < CB; ++j) {
-                double d = lane_value(row[j], j);
-                if (!(d > 0.0)) {
-                    bad = true;
-                    d = tiny;
-                }
-                const double rd = rsqrt(d);
-                if (lane == j) {
-                    row[j] = d * rd;
-                    myrd = rd;
-                } else if (lane > j) {
-                    row[j] *= rd;
-                }
-                // rank-1 update of the block's remaining columns
-#pragma unroll
-                for (int c = j + 1; c < CB; ++c) row[c] -= row[j] * lane_value(row[j], c);
+                for (int c = 0; c < CB; ++c) a[c] = src[tr + CLD * c];
+                chol_block<true, 0>(a, even ? tr : -1, tiny, neg);
             }
-            // column `lane` of D^{-1}: x_r = (delta_{r,lane} - sum_{d<r} L(r, d) x_d) / L(r, r)
-            double x[CB];
+            if (tg == 1) {   // column tr of D^{-1}
 #pragma unroll
-            for (int r = 0; r < CB; ++r) {
-                double sacc = (r == lane) ? 1.0 : 0.0;
-#pragma unroll
-                for (int d = 0; d < r; ++d) sacc -= lane_value(row[d], r) * x[d];
-                x[r] = sacc * lane_value(myrd, r);
+                for (int c = 0; c < CB; ++c) dk[c + CLD * tr] = c >= tr ? a[c] : 0.0;
             }
-            // row `lane` of the block: L(lane, c) for c <= lane, D^{-1}(c, lane) above
-            if (lane < CB) {
+            if (Rout && tg == 0 && k0 + tr < n) {
 #pragma unroll
-                for (int c = 0; c < CB; ++c) s_l[k0 + lane + ld * (k0 + c)] = (c <= lane) ? row[c] : x[c];
-                s_rd[k0 + lane] = myrd;
+                for (int c = 0; c < CB; ++c)
+                    if (k0 + c < n) Rout[k0 + c + n * (k0 + tr)] = c <= tr ? a[c] : 0.0;
+            }
+        } else if (kb) {
+            // the rest of the previous panel's update: lower tiles of A, then W
+            const int nt = nb - kb, na = nt * (nt + 1) / 2;
+            for (int q = wave; q < na + nt * kb; q += NW - 1) {
+                if (q < na) {
+                    int bi = 0;
+                    while ((bi + 1) * (bi + 2) / 2 <= q) ++bi;
+                    const int bj = kb + q - bi * (bi + 1) / 2;
+                    bi += kb;
+                    update(bi, s_l + CB * (bi + CLD * bj), false, s_p + CB * bj, TransX());
+                } else {
+                    const int bi = kb + (q - na) % nt, bj = (q - na) / nt;
+                    update(bi, s_l + CB * (bi + CLD * bj), bj == kp, s_l + CB * (kp + CLD * bj), PlainX());
+                }
             }
         }
-        __syncthreads();
-        if (t0 >= np) break;
-        // 2. panel P(bi) = A(bi, K) D^{-T}, one row tile per wave at a time;
-        //    D^{-T}(k, c) = D^{-1}(c, k): the upper half for c > k, 1 / L(k, k) for c = k
-        for (int bi = kb + 1 + wave; bi < nb; bi += NW) {
-            const int ri = CB * bi;
-            f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+        chol_sync();
+        if (wave == NW - 1) {   // D^{-T} into Rinv
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                const int k = 4 * kk + tg;
-                const double a = s_l[ri + tr + ld * (k0 + k)];
-                const double dup = s_l[k0 + k + ld * (k0 + tr)];
-                const double b = tr > k ? dup : (tr == k ? s_rd[k0 + k] : 0.0);
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) s_l[ri + tg + 4 * v + ld * (k0 + tr)] = acc[v];
+            for (int v = 0; v < 4; ++v)
+                if (k0 + tr < n && k0 + tg + 4 * v < n) Rinv[k0 + tr + n * (k0 + tg + 4 * v)] = dk[cr + 4 * v];
         }
-        __syncthreads();
-        // 3. trailing update A(bi, bj) -= P(bi) P(bj)^T on the matrix cores,
-        //    lower-triangle tiles bi >= bj > kb, one tile per wave at a time
-        const int nt = nb - kb - 1;
-        for (int q = wave; q < nt * (nt + 1) / 2; q += NW) {
-            int bi = 0;
-            while ((bi + 1) * (bi + 2) / 2 <= q) ++bi;
-            const int bj = q - bi * (bi + 1) / 2;
-            const int ri = t0 + CB * bi, cj = t0 + CB * bj;
+        // P(b)^T = D^{-1} A(b, K)^T for b > kb, L^{-1}(K, b) = D^{-1} W(K, b) for b < kb
+        for (int q = wave; q < nb - 1; q += NW) {
+            const bool below = q >= kb;
+            const int i0 = CB * (below ? q + 1 : q);
             f64x4 acc;
+            if (below) {
+                acc = solve(dk, s_l + i0 + CLD * k0, TransX());
 #pragma unroll
-            for (int v = 0; v < 4; ++v) acc[v] = s_l[ri + tg + 4 * v + ld * (cj + tr)];
-            // A operand: P(ri.., k) = s_l[ri + i + ld * (k0 + k)];  B operand:
-            // P^T(k, cj..) = s_l[cj + j + ld * (k0 + k)], i.e. b(k, j) with ldb swapped
+                for (int v = 0; v < 4; ++v) s_p[i0 + rc + 4 * v * CLD] = acc[v];
+            } else {
+                acc = solve(dk, s_l + k0 + CLD * i0, PlainX());
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                const double a = -s_l[ri + tr + ld * (k0 + 4 * kk + tg)];
-                const double b = s_l[cj + tr + ld * (k0 + 4 * kk + tg)];
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+                for (int v = 0; v < 4; ++v) s_l[k0 + CLD * i0 + cr + 4 * v] = acc[v];
             }
+            // R(K, b) or Rinv(b, K)
+            double *out = below ? Rout : Rinv;
+            if (!out) continue;
+            out += below ? k0 + n * i0 : i0 + n * k0;
+            const int o = below ? tg + n * tr : tr + n * tg, ov = below ? 4 : 4 * n;
+            if (max(k0, i0) + CB <= n) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) s_l[ri + tg + 4 * v + ld * (cj + tr)] = acc[v];
+                for (int v = 0; v < 4; ++v) out[o + ov * v] = acc[v];
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (i0 + tr < n && k0 + tg + 4 * v < n) out[o + ov * v] = acc[v];
+            }
         }
-        __syncthreads();
+        chol_sync();
     }
     if (bad && flag) flag[0] = 2;
-    if (Rout)
-        for (int j = wave; j < n; j += NW)       // R(i, j) = L(j, i)
-            for (int i = lane; i < n; i += 64) Rout[i + (int64_t)n * j] = (i <= j) ? s_l[j + ld * i] : 0.0;
-    __syncthreads();
-    // in-place inverse, block columns from the last one
-    for (int kb = nb - 1; kb >= 0; --kb) {
-        const int k0 = kb * CB, t0 = k0 + CB;
-        // D^{-1} of the diagonal block (lower) from its kept transpose
-        for (int e = tid; e < CB * CB; e += NTH) {
-            const int r = e % CB, c = e / CB;
-            s_dinv[e] = r > c ? s_l[k0 + c + ld * (k0 + r)] : (r == c ? s_rd[k0 + r] : 0.0);
-        }
-        // T(bi) = sum_{bj = kb+1..bi} Linv(bi, bj) L(bj, kb): one row tile per wave
-        for (int bi = kb + 1 + wave; bi < nb; bi += NW) {
-            const int ri = CB * bi;
-            f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-            for (int bj = kb + 1; bj <= bi; ++bj) {
-                const int cj = CB * bj;
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                    const double a = s_l[ri + tr + ld * (cj + 4 * kk + tg)];   // Linv(ri + r, cj + k)
-                    const double b = s_l[cj + 4 * kk + tg + ld * (k0 + tr)];   // L(cj + k, k0 + c)
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) s_tmp[(ri - t0) + tg + 4 * v + np * tr] = acc[v];
-        }
-        __syncthreads();
-        // Linv(bi, kb) = -T(bi) Dinv;  Linv(kb, kb) = Dinv
-        for (int bi = kb + 1 + wave; bi < nb; bi += NW) {
-            const int ri = CB * bi;
-            f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                const double a = -s_tmp[(ri - t0) + tr + np * (4 * kk + tg)];
-                const double b = s_dinv[(4 * kk + tg) + CB * tr];
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) s_l[ri + tg + 4 * v + ld * (k0 + tr)] = acc[v];
-        }
-        for (int e = tid; e < CB * CB; e += NTH) {
-            const int r = e % CB, c = e / CB;
-            s_l[k0 + r + ld * (k0 + c)] = s_dinv[e];
-        }
-        __syncthreads();
-    }
-    for (int j = wave; j < n; j += NW)           // Rinv(i, j) = Linv(j, i)
-        for (int i = lane; i < n; i += 64) Rinv[i + (int64_t)n * j] = (i <= j) ? s_l[j + ld * i] : 0.0;
 }
 
 }  // namespace sth

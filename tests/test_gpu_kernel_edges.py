@@ -137,3 +137,20 @@ def test_error_sums_in_vectors(api, dims, ranks, dtype):
     Xo = oracle.reconstruct(G.astype(np.float64), U)
     tol = 1e-12 if dtype == "float64" else 1e-5
     np.testing.assert_allclose(out, [np.sum((X - Xo) ** 2), np.sum(X.astype(np.float64) ** 2)], rtol=tol)
+
+
+@pytest.mark.parametrize("R", [1, 2, 15, 16, 17, 32, 33, 64, 65, 80, 113, 127, 128])
+def test_cholesky_qr_orders(api, R):
+    """The blocked Cholesky and its inverse at the edges of its 16-column panels,
+    through the ALS branch's QR of an I x R basis of an exactly rank-R unfolding.
+    Two Cholesky-QR passes leave ||U^T U - I|| <= 6 (I R + R (R + 1)) u (Yamamoto
+    et al., 2015); the basis spans the unfolding within the same bound."""
+    I = 300
+    rng = np.random.default_rng(R)
+    Y = np.asfortranarray(rng.standard_normal((I, R)) @ rng.standard_normal((R, 3 * R)))
+    Z, U, _, _ = api.mode_step(api.to_device(Y), 0, R, "als", "fp64", "fp64", seed=3)
+    U = api.to_numpy(U)
+    bound = 6 * (I * R + R * (R + 1)) * 1.1e-16
+    assert np.linalg.norm(U.T @ U - np.eye(R), 2) <= bound
+    assert np.linalg.norm(Y - U @ (U.T @ Y), 2) <= bound * np.linalg.norm(Y, 2)
+    np.testing.assert_allclose(api.to_numpy(Z), U.T @ Y, rtol=0, atol=bound * np.linalg.norm(Y, 2))
