@@ -26,8 +26,9 @@ namespace sth {
 //     the matrix cores.  W(B, J) (J <= K) lies where L(B, J) was.  The first wave
 //     updates the next diagonal block and goes on to factor it while the others
 //     do the rest: two barriers per panel.
-// Writes R = L^T (upper, may be NULL) and Rinv = L^{-T} (upper), n x n, tile by
-// tile as they become final.  A non-positive pivot sets flag[0] = 2 and is
+// Writes R = L^T (upper) and Rinv = L^{-T} (upper), n x n, tile by tile as they
+// become final; either may be NULL.  L^{-1} is left in LDS (lower tiles; the
+// upper ones hold other things).  A non-positive pivot sets flag[0] = 2 and is
 // replaced by a tiny positive one so that the run continues.
 //
 // Bound by the serial chain of the diagonal blocks.  Against the form with lane
@@ -181,7 +182,7 @@ __device__ __forceinline__ void chol_body(const double *__restrict__ G, int n, i
         for (int j = wave - 1; j < n; j += NW - 1)
             for (int i = (j / CB + 1) * CB + lane; i < n; i += 64) {
                 if (Rout) Rout[i + n * j] = 0.0;
-                Rinv[i + n * j] = 0.0;
+                if (Rinv) Rinv[i + n * j] = 0.0;
             }
     }
     // tile c -= P(b) X (c begun as 0 where fresh): X(k, j) = x[XK k + XJ j]
@@ -255,7 +256,7 @@ __device__ __forceinline__ void chol_body(const double *__restrict__ G, int n, i
             }
         }
         chol_sync();
-        if (wave == NW - 1) {   // D^{-T} into Rinv
+        if (Rinv && wave == NW - 1) {   // D^{-T} into Rinv
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 if (k0 + tr < n && k0 + tg + 4 * v < n) Rinv[k0 + tr + n * (k0 + tg + 4 * v)] = dk[cr + 4 * v];

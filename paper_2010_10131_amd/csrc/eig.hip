@@ -28,6 +28,7 @@
 // Selection: eigenvalues in descending order, the R leading eigenvectors
 // signed so that their entry of largest magnitude is positive (first index
 // on ties).
+#include "chol_body.h"
 #include "common.h"
 #include "eig_body.h"
 #include "internal.h"
@@ -107,74 +108,137 @@ __global__ __launch_bounds__(TE_T) void teig_kernel(const double *__restrict__ S
 }
 
 // ---- subspace-iteration products: one 16 x 16 tile of C per workgroup on
-// the FP64 matrix cores, the four waves splitting the contraction (steps of
-// 4, four steps' loads issued together), their partial tiles summed in LDS
-// in a fixed order.  Out-of-range rows and columns read clamped addresses
-// and use zeros.  All take a gate (see gate_open).
-constexpr int SI_T = 256;
+// the FP64 matrix cores, the waves splitting the contraction in steps of 16
+// (lane group g takes 4 g .. 4 g + 3 of a step, so that an operand walked along
+// the contraction is read in whole 128-byte lines), their partial tiles summed
+// in LDS in a fixed order.  Out-of-range rows and columns read clamped addresses
+// and use zeros.  All take a gate (see gate_open).  They are bound by the
+// latency of a wave's successive steps, not by the matrix cores: hence many
+// waves per tile, 16- and 32-byte loads and two steps in flight.  n = 512, p = 80:
+// S Q 5.6 us and Q^T Q 6.4 us, against 7.2 and 9.6 with four waves per tile and
+// 8-byte loads, one step at a time (an empty launch in the same trace: 4.4).
+constexpr int SI_NN_T = 512, SI_TN_T = 1024;
 
-// C (m x q) = A (m x k) B (k x q).  TRI_B: B upper triangular (k = q), so a
-// tile of columns j0.. needs k < j0 + 16 only.  NS: C = 1.5 A - 0.5 A B, one
-// Newton-Schulz step toward orthonormal columns (B = A^T A, k = q).
-template <bool TRI_B, bool NS>
-__global__ __launch_bounds__(SI_T) void si_nn_kernel(int m, int q, int k, const double *__restrict__ A, int64_t lda,
-                                                    const double *__restrict__ B, int64_t ldb,
-                                                    double *__restrict__ C, int64_t ldc,
-                                                    const double *__restrict__ gate, int gate_R,
-                                                    double gate_tol) {
+// four consecutive elements along the contraction
+template <bool CONTIG>
+__device__ __forceinline__ void si_load4(double (&v)[4], const double *p, int64_t stride) {
+    if constexpr (CONTIG) __builtin_memcpy(v, p, 32);
+    else
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = p[stride * u];
+}
+
+// acc = sum over k < kmax of a(k) b(k), this wave's share; pa and pb point at
+// this lane's row and column, sa and sb are their strides along k (1 where CA,
+// CB1).  Two steps' loads are in flight.
+template <bool CA, bool CB1>
+__device__ __forceinline__ f64x4 si_tile(const double *pa, int64_t sa, bool rok, const double *pb, int64_t sb,
+                                         bool cok, int kmax, int wave, int nw, int tg) {
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    for (int s0 = 32 * wave; s0 < kmax; s0 += 32 * nw) {
+        double a[2][4], b[2][4];
+        if (s0 + 32 <= kmax) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int kk = s0 + 16 * h + 4 * tg;
+                si_load4<CA>(a[h], pa + sa * kk, sa);
+                si_load4<CB1>(b[h], pb + sb * kk, sb);
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (!rok) a[h][u] = 0.0;
+                    if (!cok) b[h][u] = 0.0;
+                }
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int kk = s0 + 16 * h + 4 * tg + u;
+                    const bool ok = kk < kmax;
+                    const int kc = ok ? kk : 0;
+                    a[h][u] = pa[sa * kc];
+                    b[h][u] = pb[sb * kc];
+                    if (!(ok && rok)) a[h][u] = 0.0;
+                    if (!(ok && cok)) b[h][u] = 0.0;
+                }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[h][u], b[h][u], acc, 0, 0, 0);
+    }
+    return acc;
+}
+
+// The summed tile: thread tid < 256 gets the element of tile row
+// (tid >> 4 & 3) + 4 (tid >> 6), column tid & 15.
+template <int NW>
+__device__ __forceinline__ double si_sum(double (&s_acc)[NW][256], f64x4 acc, int wave, int lane, int tid) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s_acc[wave][64 * v + lane] = acc[v];
+    __syncthreads();
+    double c = 0.0;
+    if (tid < 256)
+#pragma unroll
+        for (int w = 0; w < NW; ++w) c += s_acc[w][tid];
+    return c;
+}
+
+// Z (n x q) = S Q.
+__global__ __launch_bounds__(SI_NN_T) void si_sq_kernel(int n, int q, const double *__restrict__ S,
+                                                       const double *__restrict__ Q, int64_t ldq,
+                                                       double *__restrict__ Z, int64_t ldz,
+                                                       const double *__restrict__ gate, int gate_R,
+                                                       double gate_tol) {
     if (!gate_open(gate, gate_R, gate_tol)) return;
-    __shared__ f64x4 s_acc[3][64];
+    constexpr int NW = SI_NN_T / 64;
+    __shared__ double s_acc[NW][256];
+    const int mt = (n + 15) >> 4;
+    const int bi = blockIdx.x % mt, bj = blockIdx.x / mt;
+    const int i0 = bi << 4, j0 = bj << 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tr = lane & 15, tg = lane >> 4;
+    const int ia = min(i0 + tr, n - 1), jb = min(j0 + tr, q - 1);
+    // D(row = column of Q, col = row of S): the stores run along the rows
+    const f64x4 acc = si_tile<true, false>(Q + ldq * jb, 1, j0 + tr < q, S + ia, n, i0 + tr < n, n, wave, NW, tg);
+    const double z = si_sum<NW>(s_acc, acc, wave, lane, tid);
+    const int col = j0 + tg + 4 * wave, row = i0 + tr;
+    if (tid < 256 && row < n && col < q) Z[row + ldz * col] = z;
+}
+
+// C = 1.5 A - 0.5 A B, one Newton-Schulz step toward orthonormal columns
+// (A m x q, B = A^T A).
+__global__ __launch_bounds__(SI_NN_T) void si_ns_kernel(int m, int q, const double *__restrict__ A, int64_t lda,
+                                                       const double *__restrict__ B, double *__restrict__ C,
+                                                       const double *__restrict__ gate, int gate_R,
+                                                       double gate_tol) {
+    if (!gate_open(gate, gate_R, gate_tol)) return;
+    constexpr int NW = SI_NN_T / 64;
+    __shared__ double s_acc[NW][256];
     const int mt = (m + 15) >> 4;
     const int bi = blockIdx.x % mt, bj = blockIdx.x / mt;
     const int i0 = bi << 4, j0 = bj << 4;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tr = lane & 15, tg = lane >> 4;
-    const int kmax = TRI_B ? min(k, j0 + 16) : k;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tr = lane & 15, tg = lane >> 4;
     const int ia = min(i0 + tr, m - 1), jb = min(j0 + tr, q - 1);
-    const bool rok = i0 + tr < m, cok = j0 + tr < q;
-    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-    for (int s0 = 4 * wave; 4 * s0 < kmax; s0 += 16) {
-        double a[4], b[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int kk = 4 * (s0 + u) + tg;
-            const bool ok = kk < kmax;
-            const int kc = ok ? kk : 0;
-            a[u] = A[ia + lda * kc];
-            b[u] = B[kc + ldb * jb];
-            if (!(ok && rok)) a[u] = 0.0;
-            if (!(ok && cok)) b[u] = 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc, 0, 0, 0);
-    }
-    if (wave > 0) s_acc[wave - 1][lane] = acc;
-    __syncthreads();
-    if (wave == 0) {
-#pragma unroll
-        for (int w = 0; w < 3; ++w) acc += s_acc[w][lane];
-        const int col = j0 + tr;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int row = i0 + tg + 4 * v;
-            if (row < m && col < q) {
-                double c = acc[v];
-                if (NS) c = 1.5 * A[row + lda * col] - 0.5 * c;
-                C[row + ldc * col] = c;
-            }
-        }
-    }
+    const f64x4 acc = si_tile<true, false>(B + (int64_t)q * jb, 1, j0 + tr < q, A + ia, lda, i0 + tr < m, q, wave, NW, tg);
+    const double c = si_sum<NW>(s_acc, acc, wave, lane, tid);
+    const int col = j0 + tg + 4 * wave, row = i0 + tr;
+    if (tid < 256 && row < m && col < q) C[row + lda * col] = 1.5 * A[row + lda * col] - 0.5 * c;
 }
 
 // C (p x q) = A^T B with A (k x p), B (k x q).  SYM: B = A, only the tiles
 // on and below the diagonal are formed and each is written to both halves.
 template <bool SYM>
-__global__ __launch_bounds__(SI_T) void si_tn_kernel(int p, int q, int k, const double *__restrict__ A, int64_t lda,
-                                                    const double *__restrict__ B, int64_t ldb,
-                                                    double *__restrict__ C, int64_t ldc,
-                                                    const double *__restrict__ gate, int gate_R,
-                                                    double gate_tol) {
+__global__ __launch_bounds__(SI_TN_T) void si_tn_kernel(int p, int q, int k, const double *__restrict__ A, int64_t lda,
+                                                       const double *__restrict__ B, int64_t ldb,
+                                                       double *__restrict__ C, int64_t ldc,
+                                                       const double *__restrict__ gate, int gate_R,
+                                                       double gate_tol) {
     if (!gate_open(gate, gate_R, gate_tol)) return;
-    __shared__ f64x4 s_acc[3][64];
+    constexpr int NW = SI_TN_T / 64;
+    __shared__ double s_acc[NW][256];
     int bi, bj;
     if (SYM) {
         const int t = blockIdx.x;
@@ -187,38 +251,61 @@ __global__ __launch_bounds__(SI_T) void si_tn_kernel(int p, int q, int k, const 
         bj = blockIdx.x / pt;
     }
     const int i0 = bi << 4, j0 = bj << 4;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tr = lane & 15, tg = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tr = lane & 15, tg = lane >> 4;
     const int ia = min(i0 + tr, p - 1), jb = min(j0 + tr, q - 1);
-    const bool rok = i0 + tr < p, cok = j0 + tr < q;
-    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-    for (int s0 = 4 * wave; 4 * s0 < k; s0 += 16) {
-        double a[4], b[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int kk = 4 * (s0 + u) + tg;
-            const bool ok = kk < k;
-            const int kc = ok ? kk : 0;
-            a[u] = A[kc + lda * ia];
-            b[u] = B[kc + ldb * jb];
-            if (!(ok && rok)) a[u] = 0.0;
-            if (!(ok && cok)) b[u] = 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc, 0, 0, 0);
+    const f64x4 acc = si_tile<true, true>(A + lda * ia, 1, i0 + tr < p, B + ldb * jb, 1, j0 + tr < q, k, wave, NW, tg);
+    const double c = si_sum<NW>(s_acc, acc, wave, lane, tid);
+    const int row = i0 + tg + 4 * wave, col = j0 + tr;
+    if (tid < 256 && row < p && col < q) {
+        C[row + ldc * col] = c;
+        if (SYM && bi != bj) C[col + ldc * row] = c;
     }
-    if (wave > 0) s_acc[wave - 1][lane] = acc;
-    __syncthreads();
-    if (wave == 0) {
+}
+
+// Q = A R^{-1} with G (+ shift) = R^T R (chol_body), A and Q n x p, p <= 128.
+// Every workgroup factors G for itself and takes 16 rows of A, which it has
+// loaded before: the redundant factorizations run side by side, where a
+// factorization in one workgroup and a product after it cost another launch and
+// the trip of R^{-1} through memory (n = 512, p = 80: 16.5 us, against 15 + 7).
+constexpr int SI_CQ_T = 512;
+__global__ __launch_bounds__(SI_CQ_T) void si_cholqr_kernel(int n, int p, const double *__restrict__ A, int64_t lda,
+                                                           const double *__restrict__ G, double shift_rel,
+                                                           double *__restrict__ Q, int64_t *__restrict__ flag,
+                                                           const double *__restrict__ gate, int gate_R,
+                                                           double gate_tol) {
+    if (!gate_open(gate, gate_R, gate_tol)) return;
+    constexpr int NW = SI_CQ_T / 64, AV = CB * 128 / SI_CQ_T;
+    extern __shared__ __align__(16) double s_l[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tr = lane & 15, tg = lane >> 4;
+    const int i0 = CB * blockIdx.x, np = chol_np(p);
+    double av[AV];   // row tid & 15, column (tid >> 4) + 32 u
 #pragma unroll
-        for (int w = 0; w < 3; ++w) acc += s_acc[w][lane];
-        const int col = j0 + tr;
+    for (int u = 0; u < AV; ++u) {
+        const int i = i0 + (tid & 15), k = (tid >> 4) + SI_CQ_T / 16 * u;
+        av[u] = i < n && k < p ? A[i + lda * k] : 0.0;
+    }
+    chol_body<SI_CQ_T>(G, p, p, shift_rel, nullptr, nullptr, blockIdx.x == 0 ? flag : nullptr);
+    // the panel's place is free now: A(i, k) = s_a[k + CLD i]; R^{-1}(k, j) = L^{-1}(j, k)
+    double *s_a = s_l + np * CLD;
+#pragma unroll
+    for (int u = 0; u < AV; ++u) {
+        const int k = (tid >> 4) + SI_CQ_T / 16 * u;
+        if (k < np) s_a[k + CLD * (tid & 15)] = av[u];
+    }
+    __syncthreads();
+    for (int j0 = CB * wave; j0 < np; j0 += CB * NW) {
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+        for (int k0 = 0; k0 <= j0; k0 += CB)
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                const int k = k0 + 4 * kk + tg;
+                // D(row = j, col = i): stores run along the rows of A
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(s_l[j0 + tr + CLD * k], s_a[k + CLD * tr], acc, 0, 0, 0);
+            }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int row = i0 + tg + 4 * v;
-            if (row < p && col < q) {
-                C[row + ldc * col] = acc[v];
-                if (SYM && bi != bj) C[col + ldc * row] = acc[v];
-            }
+            const int j = j0 + tg + 4 * v;
+            if (j < p && i0 + tr < n) Q[i0 + tr + lda * j] = acc[v];
         }
     }
 }
@@ -228,7 +315,10 @@ __global__ __launch_bounds__(SI_T) void si_tn_kernel(int p, int q, int k, const 
 //   res[r] = ||Z W(:, r) - theta_r U(:, r)|| with Z = S Q (the Ritz residual);
 //   lam[r] = theta_r; res[R] = |theta_1| (workgroup 0); res2 (may be null)
 //   gets the same values.  Gated (see gate_open); gate must not be res.
-__global__ __launch_bounds__(256) void rr_finish_kernel(const double *__restrict__ Q, const double *__restrict__ Zs,
+// Bound by what one CU reads (Q and Z whole): two rows per 16-byte load and 16
+// loads in flight, 9.7 us at n = 512, p = 80 (16.4 with 8-byte loads).
+constexpr int RR_T = 512, RR_W = RR_T / 64;
+__global__ __launch_bounds__(RR_T) void rr_finish_kernel(const double *__restrict__ Q, const double *__restrict__ Zs,
                                                         int n, int p, const double *__restrict__ W,
                                                         const double *__restrict__ th, int R,
                                                         double *__restrict__ U, double *__restrict__ lam,
@@ -237,28 +327,64 @@ __global__ __launch_bounds__(256) void rr_finish_kernel(const double *__restrict
     if (!gate_open(gate, R, gate_tol)) return;
     const int r = blockIdx.x, tid = threadIdx.x;
     __shared__ double s_w[SI_BLOCK_MAX];
-    __shared__ double s_ss[4], s_bv[4], s_vv[4];
-    __shared__ int s_bi[4];
-    __shared__ double s_sign;
-    for (int k = tid; k < p; k += 256) s_w[k] = W[k + (int64_t)p * r];
+    __shared__ double s_ss[RR_W], s_bv[RR_W], s_vv[RR_W];
+    __shared__ int s_bi[RR_W];
+    __shared__ double s_sign, s_half[4][256];
+    for (int k = tid; k < p; k += RR_T) s_w[k] = W[k + (int64_t)p * r];
     __syncthreads();
     const double t = th[r];
     double ss = 0.0, best = -1.0, bval = 0.0;
     int arg = 0;
-    for (int i = tid; i < n; i += 256) {
-        double u = 0.0, z = 0.0;
-        for (int k = 0; k < p; ++k) {
-            u += Q[i + (int64_t)n * k] * s_w[k];
-            z += Zs[i + (int64_t)n * k] * s_w[k];
+    // two rows per thread in 16-byte loads, the two halves of the workgroup
+    // splitting the contraction
+    const int half = tid >> 8, kh = (p + 1) >> 1, kb = half * kh, ke = min(p, kb + kh);
+    for (int r0 = 0; r0 < n; r0 += 512) {
+        const int i = r0 + 2 * (tid & 255);
+        const int ic = min(i, n - 2);   // n > 128
+        double u[2] = {0.0, 0.0}, z[2] = {0.0, 0.0};
+        if (i < n)
+            for (int k0 = kb; k0 < ke; k0 += 8) {
+                double qv[8][2], zv[8][2];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const int64_t o = ic + (int64_t)n * min(k0 + c, ke - 1);
+                    __builtin_memcpy(qv[c], Q + o, 16);
+                    __builtin_memcpy(zv[c], Zs + o, 16);
+                }
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const double w = k0 + c < ke ? s_w[k0 + c] : 0.0;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        u[h] += qv[c][h] * w;
+                        z[h] += zv[c][h] * w;
+                    }
+                }
+            }
+        __syncthreads();   // s_half is free
+        if (half) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                s_half[2 * h][tid & 255] = u[h];
+                s_half[2 * h + 1][tid & 255] = z[h];
+            }
         }
-        const double d = z - t * u;
-        ss += d * d;
-        U[i + (int64_t)n * r] = u;
-        if (fabs(u) > best) {
-            best = fabs(u);
-            arg = i;
-            bval = u;
-        }
+        __syncthreads();
+        if (!half)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                // rows ic and ic + 1: only those not taken by another thread
+                const int row = ic + h;
+                if (i >= n || row < i || row >= n) continue;
+                const double uu = u[h] + s_half[2 * h][tid], d = z[h] + s_half[2 * h + 1][tid] - t * uu;
+                ss += d * d;
+                U[row + (int64_t)n * r] = uu;
+                if (fabs(uu) > best) {
+                    best = fabs(uu);
+                    arg = row;
+                    bval = uu;
+                }
+            }
     }
     for (int o = 32; o > 0; o >>= 1) {
         ss += __shfl_xor(ss, o);
@@ -280,8 +406,8 @@ __global__ __launch_bounds__(256) void rr_finish_kernel(const double *__restrict
     if (tid == 0) {
         double tot = 0.0, b = s_bv[0], v = s_vv[0];
         int a = s_bi[0];
-        for (int w = 0; w < 4; ++w) tot += s_ss[w];
-        for (int w = 1; w < 4; ++w)
+        for (int w = 0; w < RR_W; ++w) tot += s_ss[w];
+        for (int w = 1; w < RR_W; ++w)
             if (s_bv[w] > b || (s_bv[w] == b && s_bi[w] < a)) {
                 b = s_bv[w];
                 a = s_bi[w];
@@ -298,7 +424,7 @@ __global__ __launch_bounds__(256) void rr_finish_kernel(const double *__restrict
     }
     __syncthreads();
     if (s_sign < 0.0)
-        for (int i = tid; i < n; i += 256) U[i + (int64_t)n * r] = -U[i + (int64_t)n * r];
+        for (int i = tid; i < n; i += RR_T) U[i + (int64_t)n * r] = -U[i + (int64_t)n * r];
 }
 
 namespace {
@@ -320,7 +446,7 @@ constexpr double SI_RES_C = 16.0;
 constexpr int SI_ITERS_LOOSE = 2, SI_ITERS_FP64 = 3, SI_ITERS_MORE = 2;
 
 struct SiWs {
-    double *Q, *Z, *Z2, *G, *Rinv, *T, *W, *th, *res, *res2;
+    double *Q, *Z, *Z2, *G, *T, *W, *th, *res, *res2;
     double *te;   // teig scratch of the p x p Rayleigh-Ritz problem
     double *fb;   // teig scratch of the direct solve of S (fallback)
 };
@@ -334,7 +460,6 @@ SiWs si_layout(char *ws, int64_t n, int64_t p, int64_t R) {
     w.Z = d; d += n * p;
     w.Z2 = d; d += n * p;
     w.G = d; d += p * p;
-    w.Rinv = d; d += p * p;
     w.T = d; d += p * p;
     w.W = d; d += p * p;
     w.th = d; d += p;
@@ -346,24 +471,16 @@ SiWs si_layout(char *ws, int64_t n, int64_t p, int64_t R) {
 }
 
 size_t si_bytes(int64_t n, int64_t p, int64_t R) {
-    return 256 + (size_t)(3 * n * p + 4 * p * p + 3 * p + 2) * 8 + teig_scratch_doubles(p, R, true) * 8 +
+    return 256 + (size_t)(3 * n * p + 3 * p * p + 3 * p + 2) * 8 + teig_scratch_doubles(p, R, true) * 8 +
            teig_scratch_doubles(n, R, n <= TE_LDS_N) * 8 + 256;
 }
 
 size_t teig_bytes(int64_t n, int64_t R) { return 256 + teig_scratch_doubles(n, R, n <= TE_LDS_N) * 8; }
 
-hipError_t si_nn(bool tri, bool ns, int m, int q, int k, const double *A, int64_t lda, const double *B, int64_t ldb,
-                 double *C, int64_t ldc, const double *gate, int gR, double gtol, hipStream_t s) {
-    const dim3 grid((unsigned)(((m + 15) / 16) * ((q + 15) / 16)));
-    if (ns)
-        hipLaunchKernelGGL((si_nn_kernel<false, true>), grid, dim3(SI_T), 0, s, m, q, k, A, lda, B, ldb, C, ldc,
-                           gate, gR, gtol);
-    else if (tri)
-        hipLaunchKernelGGL((si_nn_kernel<true, false>), grid, dim3(SI_T), 0, s, m, q, k, A, lda, B, ldb, C, ldc,
-                           gate, gR, gtol);
-    else
-        hipLaunchKernelGGL((si_nn_kernel<false, false>), grid, dim3(SI_T), 0, s, m, q, k, A, lda, B, ldb, C, ldc,
-                           gate, gR, gtol);
+hipError_t si_sq(int n, int q, const double *S, const double *Q, int64_t ldq, double *Z, int64_t ldz,
+                 const double *gate, int gR, double gtol, hipStream_t s) {
+    const dim3 grid((unsigned)(((n + 15) / 16) * ((q + 15) / 16)));
+    hipLaunchKernelGGL(si_sq_kernel, grid, dim3(SI_NN_T), 0, s, n, q, S, Q, ldq, Z, ldz, gate, gR, gtol);
     return hipGetLastError();
 }
 
@@ -371,10 +488,10 @@ hipError_t si_tn(bool sym, int p, int q, int k, const double *A, int64_t lda, co
                  double *C, int64_t ldc, const double *gate, int gR, double gtol, hipStream_t s) {
     const int pt = (p + 15) / 16, qt = (q + 15) / 16;
     if (sym)
-        hipLaunchKernelGGL((si_tn_kernel<true>), dim3((unsigned)(pt * (pt + 1) / 2)), dim3(SI_T), 0, s, p, q, k, A,
+        hipLaunchKernelGGL((si_tn_kernel<true>), dim3((unsigned)(pt * (pt + 1) / 2)), dim3(SI_TN_T), 0, s, p, q, k, A,
                            lda, B, ldb, C, ldc, gate, gR, gtol);
     else
-        hipLaunchKernelGGL((si_tn_kernel<false>), dim3((unsigned)(pt * qt)), dim3(SI_T), 0, s, p, q, k, A, lda, B,
+        hipLaunchKernelGGL((si_tn_kernel<false>), dim3((unsigned)(pt * qt)), dim3(SI_TN_T), 0, s, p, q, k, A, lda, B,
                            ldb, C, ldc, gate, gR, gtol);
     return hipGetLastError();
 }
@@ -392,8 +509,12 @@ hipError_t cholqr_pass(const double *A, double *Q, int n, int p, double shift_re
                        const Gate &g, hipStream_t s) {
     hipError_t e;
     if ((e = si_tn(true, p, p, n, A, n, A, n, w.G, p, g.res, g.R, g.tol, s))) return e;
-    if ((e = chol_launch(w.G, p, p, shift_rel, nullptr, w.Rinv, flag, s, g.res, g.R, g.tol))) return e;
-    return si_nn(true, false, n, p, p, A, n, w.Rinv, p, Q, n, g.res, g.R, g.tol, s);
+    const size_t lds = chol_lds_bytes(p);
+    if (lds > 64 * 1024)
+        if ((e = hipFuncSetAttribute((const void *)si_cholqr_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds))) return e;
+    hipLaunchKernelGGL(si_cholqr_kernel, dim3((unsigned)((n + CB - 1) / CB)), dim3(SI_CQ_T), lds, s, n, p, A, (int64_t)n,
+                       (const double *)w.G, shift_rel, Q, flag, g.res, g.R, g.tol);
+    return hipGetLastError();
 }
 
 enum OrthKind { ORTH_MID, ORTH_QR3, ORTH_NS };
@@ -416,7 +537,9 @@ hipError_t orth(double *A, double *Q, int n, int p, OrthKind kind, SiWs &w, int6
     if ((e = cholqr_pass(w.Z2, A, n, p, 0.0, w, flag, g, s))) return e;
     if (kind == ORTH_QR3) return cholqr_pass(A, Q, n, p, 0.0, w, flag, g, s);
     if ((e = si_tn(true, p, p, n, A, n, A, n, w.G, p, g.res, g.R, g.tol, s))) return e;
-    return si_nn(false, true, n, p, p, A, n, w.G, p, Q, n, g.res, g.R, g.tol, s);
+    hipLaunchKernelGGL(si_ns_kernel, dim3((unsigned)(((n + 15) / 16) * ((p + 15) / 16))), dim3(SI_NN_T), 0, s, n, p,
+                       (const double *)A, n, (const double *)w.G, Q, g.res, g.R, g.tol);
+    return hipGetLastError();
 }
 
 hipError_t jacobi_launch(int64_t n, int64_t R, const double *S, double *U, double *lam, double tol,
@@ -519,17 +642,17 @@ hipError_t eig_launch(int64_t n, int64_t R, const double *S, double *U, double *
         const Gate g = {round ? w.res : nullptr, Ri, tol_res};
         const int iters = round ? SI_ITERS_MORE : (loose ? SI_ITERS_LOOSE : SI_ITERS_FP64);
         for (int it = 0; it < iters; ++it) {
-            if ((e = si_nn(false, false, ni, pi, ni, S, n, w.Q, n, w.Z, n, g.res, g.R, g.tol, s))) return e;
+            if ((e = si_sq(ni, pi, S, w.Q, n, w.Z, n, g.res, g.R, g.tol, s))) return e;
             const OrthKind kind = it + 1 < iters ? ORTH_MID : (loose ? ORTH_NS : ORTH_QR3);
             if ((e = orth(w.Z, w.Q, ni, pi, kind, w, si_flag, g, s))) return e;
         }
         // Rayleigh-Ritz: T = Q^T S Q, its R leading pairs (W, theta), U = Q W
-        if ((e = si_nn(false, false, ni, pi, ni, S, n, w.Q, n, w.Z, n, g.res, g.R, g.tol, s))) return e;
+        if ((e = si_sq(ni, pi, S, w.Q, n, w.Z, n, g.res, g.R, g.tol, s))) return e;
         if ((e = si_tn(false, pi, pi, ni, w.Q, n, w.Z, n, w.T, p, g.res, g.R, g.tol, s))) return e;
         if ((e = teig_launch(w.T, p, p, R, w.W, p, w.th, false, w.te, si_flag, g.res, g.tol,
                              round && flag ? flag + 3 : nullptr, s)))
             return e;
-        hipLaunchKernelGGL(rr_finish_kernel, dim3((unsigned)R), dim3(256), 0, s, w.Q, w.Z, ni, pi, w.W, w.th, Ri, U,
+        hipLaunchKernelGGL(rr_finish_kernel, dim3((unsigned)R), dim3(RR_T), 0, s, w.Q, w.Z, ni, pi, w.W, w.th, Ri, U,
                            lam, round ? w.res2 : w.res, round ? nullptr : w.res2, g.res, g.tol);
         if ((e = hipGetLastError())) return e;
     }

@@ -65,10 +65,8 @@ hipError_t gemm_tn(int m, int n, int k, const double *A, int64_t lda, const doub
                    int64_t ldc, void *ws, hipStream_t s);
 hipError_t gemm_nn(bool tb, int m, int n, int k, const double *A, int64_t lda, const double *B, int64_t ldb,
                    double *C, int64_t ldc, hipStream_t s);
-// gate (may be null): run only when gate_open(gate, gate_R, gate_tol)
 hipError_t chol_launch(const double *G, int n, int64_t ldg, double shift_rel, double *R,
-                       double *Rinv, int64_t *flag, hipStream_t s, const double *gate = nullptr,
-                       int gate_R = 0, double gate_tol = 0.0);
+                       double *Rinv, int64_t *flag, hipStream_t s);
 hipError_t sumsq_launch(int dtype, const void *x, const void *y, int64_t count, double *out,
                         double *part, int64_t *flag, hipStream_t s);
 hipError_t fill_f64(double *p, int64_t n, double v, hipStream_t s);

@@ -154,3 +154,28 @@ def test_cholesky_qr_orders(api, R):
     assert np.linalg.norm(U.T @ U - np.eye(R), 2) <= bound
     assert np.linalg.norm(Y - U @ (U.T @ Y), 2) <= bound * np.linalg.norm(Y, 2)
     np.testing.assert_allclose(api.to_numpy(Z), U.T @ Y, rtol=0, atol=bound * np.linalg.norm(Y, 2))
+
+
+@pytest.mark.parametrize("n,R", [(129, 1), (129, 110), (144, 8), (160, 32), (161, 33), (191, 60), (257, 64), (320, 112),
+                                 (511, 17), (512, 80)])
+def test_subspace_iteration_orders(api, n, R):
+    """The subspace iteration's products, Cholesky-QR and finish at the edges of
+    their tiles (16 rows and columns, 32-long contraction steps, odd and even
+    orders), on a graded spectrum.  Accepted pairs have residuals within
+    16 sqrt(n) eps ||S||, the Gram itself is within K eps of the one formed here;
+    Cholesky-QR leaves ||U^T U - I|| <= 6 (n p + p (p + 1)) u with p <= 128."""
+    rng = np.random.default_rng(n + R)
+    K = n + 3
+    sv = 0.93 ** np.arange(n)
+    Y = np.asfortranarray((np.linalg.qr(rng.standard_normal((n, n)))[0] * sv)
+                          @ np.linalg.qr(rng.standard_normal((K, n)))[0].T)
+    S = Y @ Y.T
+    _, U, ev, _ = api.mode_step(api.to_device(Y), 0, R, "eig", "fp64", "fp64")
+    U, ev = api.to_numpy(U), ev.cpu().numpy()
+    eps = 2.2e-16
+    tol = (16 * np.sqrt(n) + 2 * K) * eps
+    np.testing.assert_allclose(ev, sv[:R] ** 2, rtol=0, atol=tol)
+    assert np.linalg.norm(S @ U - U * ev, axis=0).max() <= tol
+    assert np.linalg.norm(U.T @ U - np.eye(R), 2) <= 6 * (n * 128 + 128 * 129) * eps / 2
+    top = np.abs(U).argmax(0)
+    assert np.all(U[top, np.arange(R)] > 0)
