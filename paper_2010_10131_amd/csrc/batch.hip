@@ -395,7 +395,7 @@ __device__ inline BsiWs bsi_layout(double *base, int n, int p, int R) {
 __device__ void bsi_cholqr(const double *A, double *Q, int n, int p, double shift_rel, BsiWs &w, int64_t *flag) {
     bsi_tn<true>(p, p, n, A, A, w.G);
     __syncthreads();
-    chol_body<BE_THREADS>(w.G, p, p, shift_rel, nullptr, w.Rinv, flag);
+    chol_body<BE_THREADS, true>(w.G, p, p, shift_rel, nullptr, w.Rinv, flag);
     __syncthreads();
     bsi_nn<true, false>(n, p, p, A, w.Rinv, Q);
     __syncthreads();
