@@ -72,15 +72,14 @@ __global__ __launch_bounds__(256) void batch_gram_kernel(const BatchStep *__rest
     const int64_t local = lid - pref[k];
     const int64_t P = d.L * d.M;
     if (d.L == 1 && WT >= 2) {
-        const bool v4 = (d.I & 3) == 0 && ((reinterpret_cast<uintptr_t>(Y) & 15) == 0);
+        // the 16-byte loaders need only 4-byte aligned rows
         if constexpr (WT == 2) {
-            // the 16-byte loader needs only 4-byte aligned rows
             if (d.I >= 4) {
                 gram_l1_body<PREC, 2, 2, 2, 2, true, false, true>(Y, d.I, P, d.kper, d.nkc, d.nblocks, d.gram_wg, local, part);
                 return;
             }
         }
-        if (v4)
+        if (d.I >= 4)
             gram_l1_body<PREC, WT, WT, 2, 2, true>(Y, d.I, P, d.kper, d.nkc, d.nblocks, d.gram_wg, local, part);
         else
             gram_l1_body<PREC, WT, WT, 2, 2, false>(Y, d.I, P, d.kper, d.nkc, d.nblocks, d.gram_wg, local, part);
@@ -136,12 +135,20 @@ __global__ __launch_bounds__(SK_T) void batch_gram_skinny_kernel(const BatchStep
     if (lid >= total) return;
     const int k = find_segment(pref, len, lid);
     const BatchStep &d = descs[list[k]];
-    if (bsk_ch(PREC, d.I) == 4)
-        gram_skinny_body<PREC, 4, true, true>(bsrc(d, ws, Xp), (int)d.I, d.L * d.M, d.nkc, (int)(lid - pref[k]),
-                                        (double *)(ws + d.part_off));
-    else
-        gram_skinny_body<PREC, BSK_CH, true, true>(bsrc(d, ws, Xp), (int)d.I, d.L * d.M, d.nkc, (int)(lid - pref[k]),
-                                             (double *)(ws + d.part_off));
+    const float *Y = bsrc(d, ws, Xp);
+    const int64_t P = d.L * d.M;
+    const int kc = (int)(lid - pref[k]);
+    double *part = (double *)(ws + d.part_off);
+    if (d.I < 4) {   // no whole quad to load
+        if (bsk_ch(PREC, d.I) == 4) gram_skinny_body<PREC, 4, false, 1>(Y, (int)d.I, P, d.nkc, kc, part);
+        else gram_skinny_body<PREC, BSK_CH, false, 1>(Y, (int)d.I, P, d.nkc, kc, part);
+    } else if (bsk_ch(PREC, d.I) == 4) {
+        if (d.I <= SK_MS1_MAXI) gram_skinny_body<PREC, 4, true, 1>(Y, (int)d.I, P, d.nkc, kc, part);
+        else gram_skinny_body<PREC, 4, true, SK_MS>(Y, (int)d.I, P, d.nkc, kc, part);
+    } else {
+        if (d.I <= SK_MS1_MAXI) gram_skinny_body<PREC, BSK_CH, true, 1>(Y, (int)d.I, P, d.nkc, kc, part);
+        else gram_skinny_body<PREC, BSK_CH, true, SK_MS>(Y, (int)d.I, P, d.nkc, kc, part);
+    }
 }
 
 template <int TB>

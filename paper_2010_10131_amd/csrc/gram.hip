@@ -49,22 +49,22 @@ __global__ __launch_bounds__(256) void gram_kernel(const T *__restrict__ A, cons
 template <int PREC, int WT>
 constexpr bool gram_l1_eight_waves() { return WT == 4; }
 
-template <int PREC, int WT, bool VEC4, bool FULLI>
+template <int PREC, int WT, bool FULLI>
 __global__ __launch_bounds__((gram_l1_eight_waves<PREC, WT>() ? 512 : 256)) void gram_l1_kernel(
     const float *__restrict__ Y, int64_t I, int64_t P, int64_t kper, int nkc, int nblocks,
     int64_t total_wg, double *__restrict__ partials) {
     if constexpr (gram_l1_eight_waves<PREC, WT>())
-        gram_l1_body<PREC, 4, 2, 2, 4, VEC4, FULLI>(Y, I, P, kper, nkc, nblocks, total_wg,
+        gram_l1_body<PREC, 4, 2, 2, 4, true, FULLI>(Y, I, P, kper, nkc, nblocks, total_wg,
                                                     xcd_logical_id(total_wg), partials);
     else
-        gram_l1_body<PREC, WT, WT, 2, 2, VEC4, FULLI>(Y, I, P, kper, nkc, nblocks, total_wg,
+        gram_l1_body<PREC, WT, WT, 2, 2, true, FULLI>(Y, I, P, kper, nkc, nblocks, total_wg,
                                                       xcd_logical_id(total_wg), partials);
 }
 
-template <int PREC, int CH, bool V4>
+template <int PREC, int CH, bool QUAD, int MS>
 __global__ __launch_bounds__(SK_T) void gram_skinny_kernel(const float *__restrict__ Y, int I, int64_t P,
                                                           int nkc, double *__restrict__ partials) {
-    gram_skinny_body<PREC, CH, V4>(Y, I, P, nkc, blockIdx.x, partials);
+    gram_skinny_body<PREC, CH, QUAD, MS>(Y, I, P, nkc, blockIdx.x, partials);
 }
 
 // Sums the partial blocks over the row ranges and writes the IA x IB result
@@ -244,19 +244,18 @@ GramShape gram_shape_t(int64_t IA, int64_t IB, int64_t P, bool sym, int64_t targ
 }
 
 // Skinny path geometry: CH chunks of 32 columns per stage, as many as keep
-// the loader at <= SK_TASKS tasks per thread and two stages within the LDS
+// the loader at one task per thread and two stages within the LDS
 // budget; one workgroup per CU (the LDS of a stage), each at least 4 stages.
 struct SkShape {
     int ch, nkc;
 };
 
-SkShape sk_shape(int prec, int64_t I, int64_t P, bool v4) {
+SkShape sk_shape(int prec, int64_t I, int64_t P) {
     SkShape k;
     const int NQ = prec == P_FP64 ? 4 : (prec == P_BF16X6 ? 3 : 2);
     const int64_t TBp = 32 * (int64_t)sk_ns(I);
-    const int64_t tasks_max = (int64_t)(v4 ? 1 : SK_TASKS) * SK_T, rows_per_task = v4 ? 4 : 1;
     k.ch = prec == P_BF16X6 ? 4 : 8;   // bf16x6 at 8 chunks would spill registers
-    while (k.ch > 1 && (TBp / rows_per_task * 4 * k.ch > tasks_max || 2 * k.ch * NQ * 4 * TBp * 16 > 150 * 1024)) k.ch >>= 1;
+    while (k.ch > 1 && (TBp * k.ch > SK_T || 2 * k.ch * NQ * 4 * TBp * 16 > 150 * 1024)) k.ch >>= 1;
     const int64_t cols = 32 * (int64_t)k.ch;
     k.nkc = (int)std::min<int64_t>(device_cu_count(), std::max<int64_t>(1, P / (4 * cols)));
     return k;
@@ -269,8 +268,8 @@ size_t sk_lds(int prec, int64_t I, int ch) {
 
 template <int PREC, int CH>
 hipError_t launch_skinny_ch(const float *A, int64_t I, int64_t P, const SkShape &k, double *partials, hipStream_t s) {
-    const bool v4 = I % 4 == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0;
-    auto kern = v4 ? gram_skinny_kernel<PREC, CH, true> : gram_skinny_kernel<PREC, CH, false>;
+    auto kern = I < 4 ? gram_skinny_kernel<PREC, CH, false, 1>
+                      : I <= SK_MS1_MAXI ? gram_skinny_kernel<PREC, CH, true, 1> : gram_skinny_kernel<PREC, CH, true, SK_MS>;
     const size_t lds = sk_lds(PREC, I, CH);
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -282,8 +281,7 @@ hipError_t launch_skinny_ch(const float *A, int64_t I, int64_t P, const SkShape 
 
 template <int PREC>
 hipError_t launch_skinny(const float *A, int64_t I, int64_t P, double *partials, double *S, hipStream_t s) {
-    const bool v4 = I % 4 == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0;
-    const SkShape k = sk_shape(PREC, I, P, v4);
+    const SkShape k = sk_shape(PREC, I, P);
     hipError_t e;
     switch (k.ch) {
         case 8:
@@ -310,12 +308,9 @@ hipError_t launch_gram_l1(const float *A, int64_t IA, int64_t M, const GramShape
     const int64_t total = (int64_t)g.nkc * g.nblocks;
     const int64_t per_xcd = (total + 7) / 8;
     const size_t lds = (size_t)2 * 2 * Frag<PREC>::NQ * 4 * TB * 16;
-    const bool vec = (IA % 4 == 0) && ((reinterpret_cast<uintptr_t>(A) & 15) == 0);
-    // I a multiple of the block edge: the branch-free loads
-    // (blocks of 64 and 128: whole fragment octets per thread)
-    auto kern = !vec ? gram_l1_kernel<PREC, WT, false, false>
-                     : (IA % TB == 0 ? gram_l1_kernel<PREC, WT, true, (WT >= 2)>
-                                     : gram_l1_kernel<PREC, WT, true, false>);
+    // I a multiple of the block edge: the full path's loads (blocks of 64 and 128:
+    // whole fragment octets per thread); I > SK_MAXI here, so quads fit
+    auto kern = IA % TB == 0 ? gram_l1_kernel<PREC, WT, (WT >= 2)> : gram_l1_kernel<PREC, WT, false>;
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
@@ -434,7 +429,7 @@ size_t gram_ws_bytes(int64_t IA, int64_t IB, int64_t P, bool sym) {
         const int NS = sk_ns(IA);
         for (int prec = P_FP64; prec <= P_BF16X6; ++prec)
             for (int v4 = 0; v4 < 2; ++v4)
-                b = std::max(b, (size_t)sk_shape(prec, IA, P, v4 != 0).nkc * (NS * (NS + 1) / 2) * 1024 * sizeof(double));
+                b = std::max(b, (size_t)sk_shape(prec, IA, P).nkc * (NS * (NS + 1) / 2) * 1024 * sizeof(double));
     }
     return b;
 }

@@ -2,45 +2,48 @@
 // single-tensor kernels and the batched ones.
 #pragma once
 #include "common.h"
+#include <type_traits>
 
 namespace sth {
 
 constexpr int GRAM_FLUSH = 4;  // chunks of 32 rows accumulated in FP32 before an FP64 flush
 
-// Loads the 8 consecutive rows p0..p0+7 of column i of a (L, I, M) tensor.
-template <typename T>
+// Position of an octet of rows p0 .. p0 + 7 of a (L, I, M) tensor: p0 = a + L b.
+struct GramPos {
+    int64_t a, b;
+};
+
+// Loads the 8 consecutive rows p0..p0+7 of column i (clamped) of a (L, I, M)
+// tensor, pos the place of p0; rows from pend on repeat an earlier one.  The
+// values are masked when they are stored (gram_mask): a select or a branch here
+// would wait for its loads before the chunk in hand is multiplied.  VEC: L a
+// multiple of 8, so that an octet (p0 a multiple of 8) is one contiguous run.
+template <typename T, bool VEC>
 __device__ __forceinline__ void gram_load_octet(const T *__restrict__ X, int64_t L, int64_t I,
-                                                int64_t i, int64_t p0, int64_t pend, T (&x)[8]) {
-    if (i >= I) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = (T)0;
-        return;
-    }
-    if (L == 1) {
+                                                int64_t i, GramPos pos, int64_t p0, int64_t pend, T (&x)[8]) {
+    const int64_t ic = min(i, I - 1);
+    if constexpr (VEC) {
+        __builtin_memcpy(x, X + (p0 < pend ? pos.a + L * (ic + I * pos.b) : L * ic), sizeof(x));
+    } else {
+        const T *src = X + (p0 < pend ? pos.a + L * (ic + I * pos.b) : L * ic);
+        int64_t a = pos.a;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            int64_t p = p0 + j;
-            x[j] = (p < pend) ? X[i + I * p] : (T)0;
-        }
-        return;
-    }
-    int64_t b = p0 / L;
-    int64_t a = p0 - b * L;
-    if (a + 8 <= L && p0 + 8 <= pend) {
-        const T *src = X + a + L * i + L * I * b;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = src[j];
-        return;
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        int64_t p = p0 + j;
-        x[j] = (p < pend) ? X[a + L * i + L * I * b] : (T)0;
-        if (++a == L) {
-            a = 0;
-            ++b;
+            x[j] = *src;
+            const bool wrap = a + 1 == L;
+            const int64_t d = wrap ? L * (I - 1) + 1 : 1;   // the next row of the same column
+            a = wrap ? 0 : a + 1;
+            src += p0 + j + 1 < pend ? d : 0;
         }
     }
+}
+
+// Zeroes the rows of an octet from pend on.
+template <typename T>
+__device__ __forceinline__ void gram_mask(int64_t p0, int64_t pend, T (&x)[8]) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (p0 + j >= pend) x[j] = (T)0;
 }
 
 // Unit u of a TB x 32 slab (TB columns i, 4 octets of rows).  Lanes run along
@@ -63,6 +66,10 @@ __device__ __forceinline__ int64_t xcd_logical_id(int64_t total_wg) {
 }
 
 // One workgroup of the Gram/TTT: logical id lid = row range * nblocks + block.
+// The next chunk's loads are in flight while one is multiplied; they are taken
+// unmasked and their place in the tensor is carried along (no division per
+// chunk).  512^3's later modes in bf16x6: 96 us each (108 with a branch and a
+// division at each octet's load, which waited for the loads at once).
 template <typename T, int PREC, int WT, bool SYM>
 __device__ __forceinline__ void gram_body(const T *__restrict__ A, const T *__restrict__ B,
                                           int64_t L, int64_t IA, int64_t IB, int64_t P,
@@ -115,46 +122,62 @@ __device__ __forceinline__ void gram_body(const T *__restrict__ A, const T *__re
         }
 
     T ra[UPT][8], rb[UPT][8];
-    auto load_slab = [&](int64_t pc) {
+    // units past the slab (one-tile blocks) repeat its last octet
+    int il[UPT], oct[UPT];
+    GramPos pos[UPT];
+    const int64_t q32 = KC / L, r32 = KC - q32 * L;   // a chunk further: a += r32, b += q32
+#pragma unroll
+    for (int s = 0; s < UPT; ++s) {
+        gram_unit(min((int)threadIdx.x + 256 * s, UNITS - 1), TB, lfast, il[s], oct[s]);
+        const int64_t p = pbeg + 8 * oct[s];
+        pos[s].b = p / L;
+        pos[s].a = p - pos[s].b * L;
+    }
+    auto load_slab = [&](int64_t pc, auto vec) {
+        constexpr bool VEC = decltype(vec)::value;
 #pragma unroll
         for (int s = 0; s < UPT; ++s) {
-            int u = threadIdx.x + 256 * s;
-            int il, oct;
-            gram_unit(u, TB, lfast, il, oct);
-            if (u < UNITS) {
-                gram_load_octet<T>(A, L, IA, i0 + il, pc + 8 * oct, pend, ra[s]);
-                if (!diag) gram_load_octet<T>(B, L, IB, j0 + il, pc + 8 * oct, pend, rb[s]);
+            gram_load_octet<T, VEC>(A, L, IA, i0 + il[s], pos[s], pc + 8 * oct[s], pend, ra[s]);
+            if (!diag) gram_load_octet<T, VEC>(B, L, IB, j0 + il[s], pos[s], pc + 8 * oct[s], pend, rb[s]);
+            pos[s].a += r32;
+            pos[s].b += q32;
+            if (pos[s].a >= L) {
+                pos[s].a -= L;
+                ++pos[s].b;
             }
         }
     };
-    auto store_slab = [&]() {
+    auto store_slab = [&](int64_t pc) {
+        const bool ragged = pc + KC > pend;
 #pragma unroll
         for (int s = 0; s < UPT; ++s) {
-            int u = threadIdx.x + 256 * s;
-            int il, oct;
-            gram_unit(u, TB, lfast, il, oct);
-            if (u < UNITS) {
+            if (threadIdx.x + 256 * s < UNITS) {
+                if (ragged) {
+                    gram_mask(pc + 8 * oct[s], pend, ra[s]);
+                    if (!diag) gram_mask(pc + 8 * oct[s], pend, rb[s]);
+                }
                 FragQ<PREC> f;
                 make_frag(ra[s], f.f);
 #pragma unroll
-                for (int qq = 0; qq < NQ; ++qq) sA[(qq * TB + il) * 4 + oct] = f.q[qq];
+                for (int qq = 0; qq < NQ; ++qq) sA[(qq * TB + il[s]) * 4 + oct[s]] = f.q[qq];
                 if (!diag) {
                     make_frag(rb[s], f.f);
 #pragma unroll
-                    for (int qq = 0; qq < NQ; ++qq) sB[(qq * TB + il) * 4 + oct] = f.q[qq];
+                    for (int qq = 0; qq < NQ; ++qq) sB[(qq * TB + il[s]) * 4 + oct[s]] = f.q[qq];
                 }
             }
         }
     };
 
     const int nch = (int)((pend - pbeg + KC - 1) / KC);
-    if (nch > 0) load_slab(pbeg);
     const uint4 *sBr = diag ? sA : sB;
+    auto run = [&](auto vec) {
+    if (nch > 0) load_slab(pbeg, vec);
     for (int c = 0; c < nch; ++c) {
         __syncthreads();  // previous chunk's reads are done
-        store_slab();
+        store_slab(pbeg + (int64_t)c * KC);
         __syncthreads();
-        if (c + 1 < nch) load_slab(pbeg + (int64_t)(c + 1) * KC);
+        if (c + 1 < nch) load_slab(pbeg + (int64_t)(c + 1) * KC, vec);
         if (active) {
             Frag<PREC> fa[WT], fb[WT];
 #pragma unroll
@@ -189,6 +212,9 @@ __device__ __forceinline__ void gram_body(const T *__restrict__ A, const T *__re
             }
         }
     }
+    };
+    if (L % 8 == 0) run(std::true_type());
+    else run(std::false_type());
     if (!active) return;
     // partial block (TB x TB, column-major) for (kc, q)
     double *dst = partials + ((int64_t)kc * nblocks + q) * (int64_t)TB * TB;
@@ -260,24 +286,29 @@ __device__ __forceinline__ void l1_store(uint8_t *slab, int TB, int g, int row, 
     }
 }
 
+// place of a row in a stage plane (16-byte entries): rows 16 apart differ in their
+// low bits, so that the stores (rows four apart in consecutive lanes) and the
+// fragment reads (16 consecutive rows) are both free of bank conflicts
+__device__ __forceinline__ int l1_row(int r) { return r ^ ((r >> 4) & 3); }
+
 // Waves form a WI x WJ grid over the TB x TB output block, each owning
 // WTI x WTJ tiles of 16 x 16 (TB = 16 WTI WI = 16 WTJ WJ).
-// FULLI: I is a multiple of TB and rows are 16-byte aligned, so every load is
-// one float4 with no branch (rows past the range are clamped and zeroed by a
-// select) and the prefetches are issued unconditionally (chunk index clamped;
-// a diagonal block loads its one operand twice, from cache).  Branch-free
-// loads let the compiler wait for exactly the chunk being stored instead of
-// draining every load in flight before the next ones are issued.
-// V4LD (batched mode-1 launches, any I >= 4, rows 4-byte aligned): thread
-// (parity, operand, row quad iq, group g) owns rows 4 iq .. 4 iq + 3 of one
-// operand and the 8 columns g of every chunk of its parity (threads [0, 2 TB)
-// the even chunks, the rest the odd ones): eight 16-byte loads per chunk give
-// four rows' fragments (quads past I zeroed, a quad across row I read value
-// by value); the same
-// 32 values per thread as two chunks of two operands in flight.  Its LDS
-// stores are 64 bytes apart across lanes; where the matrix cores bound the
-// Gram (bf16x6 at I = 512) the FULLI loads are faster, so the single-tensor
-// path keeps those.
+// Every load is issued unconditionally (rows and columns past the range are
+// clamped, chunks past the end repeat the last one, a diagonal block loads its
+// one operand twice, from cache) and taken as it is: rows from pend on become
+// zero when they are stored.  A branch or a select at the load makes the compiler
+// wait for the chunks in flight before the one in hand is multiplied.
+// VEC4: I >= 4, 16-byte loads of four columns (any alignment).
+// FULLI: I is a multiple of TB; see below.
+// V4LD (batched mode-1 launches, any I >= 4): thread (parity, operand, row quad
+// iq, group g) owns rows 4 iq .. 4 iq + 3 of one operand and the 8 columns g of
+// every chunk of its parity (threads [0, 2 TB) the even chunks, the rest the odd
+// ones): eight 16-byte loads per chunk give four rows' fragments; the same 32
+// values per thread as two chunks of two operands in flight.  Where the matrix
+// cores bound the Gram (bf16x6 at I = 512) the FULLI loads are faster, so the
+// single-tensor path keeps those.
+// With the selects at the loads (and, V4LD, 4-way bank conflicts of its stores)
+// the Grams of the later modes of 256 mixed tensors took 2.80 ms, now 2.12 ms.
 template <int PREC, int WTI, int WTJ, int WI, int WJ, bool VEC4, bool FULLI = false, bool V4LD = false>
 __device__ __forceinline__ void gram_l1_body(const float *__restrict__ Y, int64_t I, int64_t P,
                                              int64_t kper, int nkc, int nblocks, int64_t total_wg,
@@ -330,9 +361,7 @@ __device__ __forceinline__ void gram_l1_body(const float *__restrict__ Y, int64_
 #pragma unroll
             for (int s = 0; s < KPT; ++s) {
                 const int64_t p = pc + kq * KPT + s;
-                const int64_t pcl = p < pend ? p : pend - 1;
-                const float v = src[I * pcl];
-                rf[s] = p < pend ? v : 0.f;
+                rf[s] = src[I * (p < pend ? p : pend - 1)];
             }
             return;
         }
@@ -340,22 +369,40 @@ __device__ __forceinline__ void gram_l1_body(const float *__restrict__ Y, int64_
 #pragma unroll
         for (int s = 0; s < LPT; ++s) {
             const int64_t p = pc + ph + PH * s;
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (p < pend) {
-                const float *src = Y + I * p + col;
-                if (VEC4 && col + 4 <= I) {
-                    v = *reinterpret_cast<const float4 *>(src);
-                } else {
-                    if (col + 0 < I) v.x = src[0];
-                    if (col + 1 < I) v.y = src[1];
-                    if (col + 2 < I) v.z = src[2];
-                    if (col + 3 < I) v.w = src[3];
-                }
+            const float *src = Y + I * (p < pend ? p : pend - 1);
+            if (VEC4) {   // I >= 4; the quad across column I - 1 is read from I - 4 on
+                const f32x4u v = *reinterpret_cast<const f32x4u *>(src + min(col, I - 4));
+                r[s] = make_float4(v.x, v.y, v.z, v.w);
+            } else {
+                r[s].x = src[min(col, I - 1)];
+                r[s].y = src[min(col + 1, I - 1)];
+                r[s].z = src[min(col + 2, I - 1)];
+                r[s].w = src[min(col + 3, I - 1)];
             }
-            r[s] = v;
         }
     };
-    auto store = [&](int buf, int op, const float4 (&r)[LPT]) {
+    // pc: the chunk's first row; its rows from pend on become zero here
+    auto store = [&](int buf, int op, int64_t pc, float4 (&r)[LPT]) {
+        if (pc + KC > pend) {
+#pragma unroll
+            for (int s = 0; s < 4 * LPT; ++s) {
+                const int64_t p = FULLI ? pc + kq * KPT + s : pc + ph + PH * (s / 4);
+                if (p >= pend) (&r[0].x)[s] = 0.f;
+            }
+        }
+        if constexpr (VEC4 && !FULLI) {
+            // and moved into place here (columns from I on hold anything: they
+            // reach no output that is read)
+            const int64_t sh = (op ? j0 : i0) + 4 * iq - (I - 4);
+            if (sh > 0) {
+#pragma unroll
+                for (int s = 0; s < LPT; ++s) {
+                    r[s].x = sh == 1 ? r[s].y : (sh == 2 ? r[s].z : r[s].w);
+                    r[s].y = sh == 1 ? r[s].z : r[s].w;
+                    r[s].z = r[s].w;
+                }
+            }
+        }
         uint8_t *slab = lds + (size_t)(buf * 2 + op) * SLAB;
         if constexpr (FULLI) {
             const float *rf = &r[0].x;
@@ -403,7 +450,7 @@ __device__ __forceinline__ void gram_l1_body(const float *__restrict__ Y, int64_
             FragQ<PREC> t;
             const int row = wi * (16 * WTI) + 16 * x + (lane & 15);
 #pragma unroll
-            for (int qq = 0; qq < NQ; ++qq) t.q[qq] = sA[(qq * 4 + g) * TB + row];
+            for (int qq = 0; qq < NQ; ++qq) t.q[qq] = sA[(qq * 4 + g) * TB + (V4LD ? l1_row(row) : row)];
             fa[x] = t.f;
         }
 #pragma unroll
@@ -411,7 +458,7 @@ __device__ __forceinline__ void gram_l1_body(const float *__restrict__ Y, int64_
             FragQ<PREC> t;
             const int row = wj * (16 * WTJ) + 16 * y + (lane & 15);
 #pragma unroll
-            for (int qq = 0; qq < NQ; ++qq) t.q[qq] = sB[(qq * 4 + g) * TB + row];
+            for (int qq = 0; qq < NQ; ++qq) t.q[qq] = sB[(qq * 4 + g) * TB + (V4LD ? l1_row(row) : row)];
             fb[y] = t.f;
         }
 #pragma unroll
@@ -434,54 +481,45 @@ __device__ __forceinline__ void gram_l1_body(const float *__restrict__ Y, int64_
         static_assert(NTH == 4 * TB, "one task per thread");
         constexpr int TQ4 = TB / 4;
         const int par4 = tid / (2 * TB), op4 = (tid / TB) & 1, iq4 = (tid % TB) % TQ4, g4 = (tid % TB) / TQ4;
-        // a quad wholly inside the column is one 16-byte load (4-byte
-        // aligned when I % 4 != 0); the quad that runs past row I - 1 reads
-        // its rows below I one value at a time, so no load leaves the column
+        // 16-byte loads (4-byte aligned when I % 4 != 0); the quad that runs past
+        // row I - 1 and those after it are read from row I - 4 on
         const int64_t rq = (op4 ? j0 : i0) + 4 * iq4;
-        const bool rok4 = rq < I, full4 = rq + 4 <= I;
-        const float *src4 = Y + (rok4 ? rq : 0);
+        const int64_t rs = min(rq, I - 4);
+        const int r0 = (int)(rs - (op4 ? j0 : i0));   // its first row within the block
+        const float *src4 = Y + rs;
         float rv[4][8];
         auto load4 = [&](int cn) {
             const int64_t pc = pbeg + (int64_t)(cn < nch ? cn : nch - 1) * KC;
-            if (full4) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int64_t pp = pc + 8 * g4 + j;
-                    const int64_t pcl = pp < pend ? pp : pend - 1;
-                    const f32x4u v = *reinterpret_cast<const f32x4u *>(src4 + I * pcl);
-                    const bool in = pp < pend;
-                    rv[0][j] = in ? v.x : 0.f;
-                    rv[1][j] = in ? v.y : 0.f;
-                    rv[2][j] = in ? v.z : 0.f;
-                    rv[3][j] = in ? v.w : 0.f;
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int64_t pp = pc + 8 * g4 + j;
-                    const int64_t pcl = pp < pend ? pp : pend - 1;
-                    const bool in = rok4 && pp < pend;
-#pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) {
-                        const bool ok = in && rq + rr < I;
-                        rv[rr][j] = ok ? src4[I * pcl + (ok ? rr : 0)] : 0.f;
-                    }
-                }
+            for (int j = 0; j < 8; ++j) {
+                const int64_t pp = pc + 8 * g4 + j;
+                const f32x4u v = *reinterpret_cast<const f32x4u *>(src4 + I * (pp < pend ? pp : pend - 1));
+                rv[0][j] = v.x;
+                rv[1][j] = v.y;
+                rv[2][j] = v.z;
+                rv[3][j] = v.w;
             }
         };
-        auto store4 = [&](int buf) {
+        auto store4 = [&](int buf, int cn) {
+            const int64_t pc = pbeg + (int64_t)(cn < nch ? cn : nch - 1) * KC;
+            if (pc + KC > pend) {
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) gram_mask(pc + 8 * g4, pend, rv[rr]);
+            }
+            if (rq >= I) return;   // those rows of the slab reach no output that is read
             uint4 *sq = reinterpret_cast<uint4 *>(lds + (size_t)(buf * 2 + op4) * SLAB);
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr) {
+                if (r0 + rr < 0) continue;   // a row of the block before
                 FragQ<PREC> t;
                 make_frag(rv[rr], t.f);
 #pragma unroll
-                for (int qq = 0; qq < NQ; ++qq) sq[(qq * 4 + g4) * TB + 4 * iq4 + rr] = t.q[qq];
+                for (int qq = 0; qq < NQ; ++qq) sq[(qq * 4 + g4) * TB + l1_row(r0 + rr)] = t.q[qq];
             }
         };
         if (nch > 0) {
             load4(par4);
-            if (par4 == 0) store4(0);
+            if (par4 == 0) store4(0, 0);
         }
         __syncthreads();
         // chunk c in buffer 0 and chunk c + 1 in flight on the odd threads;
@@ -490,75 +528,41 @@ __device__ __forceinline__ void gram_l1_body(const float *__restrict__ Y, int64_
         for (int c = 0; c < nch; c += 2) {
             if (par4 == 0) load4(c + 2);
             compute(0, c);
-            if (par4 == 1) store4(1);
+            if (par4 == 1) store4(1, c + 1);
             __syncthreads();
             if (par4 == 1) load4(c + 3);
             if (c + 1 < nch) compute(1, c + 1);
-            if (par4 == 0) store4(0);
+            if (par4 == 0) store4(0, c + 2);
             __syncthreads();
         }
     } else {
     float4 ra0[LPT], rb0[LPT], ra1[LPT], rb1[LPT];
     auto prefetch = [&](int cn, float4 (&ra)[LPT], float4 (&rb)[LPT]) {
-        if (FULLI) {
-            const int64_t pc = pbeg + (int64_t)(cn < nch ? cn : nch - 1) * KC;
-            load(pc, i0, ra);
-            load(pc, j0, rb);
-        } else if (cn < nch) {
-            load(pbeg + (int64_t)cn * KC, i0, ra);
-            if (!diag) load(pbeg + (int64_t)cn * KC, j0, rb);
-        }
+        const int64_t pc = pbeg + (int64_t)(cn < nch ? cn : nch - 1) * KC;
+        load(pc, i0, ra);
+        load(pc, j0, rb);
     };
-    if (FULLI && nch > 0) {
+    auto store2 = [&](int buf, int cn, float4 (&ra)[LPT], float4 (&rb)[LPT]) {
+        const int64_t pc = pbeg + (int64_t)(cn < nch ? cn : nch - 1) * KC;
+        store(buf, 0, pc, ra);
+        if (!diag) store(buf, 1, pc, rb);
+    };
+    if (nch > 0) {
         prefetch(0, ra0, rb0);
         prefetch(1, ra1, rb1);
-        store(0, 0, ra0);
-        store(0, 1, rb0);
-    } else if (nch > 0) {
-        load(pbeg, i0, ra0);
-        if (!diag) load(pbeg, j0, rb0);
-        if (nch > 1) {
-            load(pbeg + KC, i0, ra1);
-            if (!diag) load(pbeg + KC, j0, rb1);
-        }
-        store(0, 0, ra0);
-        if (!diag) store(0, 1, rb0);
+        store2(0, 0, ra0, rb0);
     }
     __syncthreads();
-    if constexpr (FULLI) {
-        // the same two-stage pipeline with every load and LDS store issued
-        // unconditionally (clamped chunks past the end are stored and never
-        // multiplied); only the matrix-core work of a missing odd chunk is skipped
-        for (int c = 0; c < nch; c += 2) {
-            prefetch(c + 2, ra0, rb0);
-            compute(0, c);
-            store(1, 0, ra1);
-            store(1, 1, rb1);
-            __syncthreads();
-            prefetch(c + 3, ra1, rb1);
-            if (c + 1 < nch) compute(1, c + 1);
-            store(0, 0, ra0);
-            store(0, 1, rb0);
-            __syncthreads();
-        }
-    } else
+    // chunk c in buffer 0, chunk c + 1 in flight in ra1 / rb1; every load is issued
+    // unconditionally (chunks past the end repeat the last one and are not multiplied)
     for (int c = 0; c < nch; c += 2) {
-        // chunk c in buffer 0; chunk c+1 in flight in ra1/rb1
         prefetch(c + 2, ra0, rb0);
         compute(0, c);
-        if (c + 1 < nch) {
-            store(1, 0, ra1);
-            if (!diag) store(1, 1, rb1);
-        }
+        store2(1, c + 1, ra1, rb1);
         __syncthreads();
-        if (c + 1 >= nch) break;
-        // chunk c+1 in buffer 1; chunk c+2 in flight in ra0/rb0
         prefetch(c + 3, ra1, rb1);
-        compute(1, c + 1);
-        if (c + 2 < nch) {
-            store(0, 0, ra0);
-            if (!diag) store(0, 1, rb0);
-        }
+        if (c + 1 < nch) compute(1, c + 1);
+        store2(0, c + 2, ra0, rb0);
         __syncthreads();
     }
     }
@@ -595,13 +599,20 @@ __device__ __forceinline__ void gram_l1_body(const float *__restrict__ Y, int64_
 constexpr int SK_MAXI = 160;
 constexpr int SK_W = 8, SK_T = 64 * SK_W;
 constexpr int SK_MS = 2;      // super tiles per wave: 15 lower 32 x 32 tiles at I = 160
-constexpr int SK_TASKS = 4;   // loader tasks per thread and stage
+constexpr int SK_MS1_MAXI = 96;   // one super tile per wave is enough: 6 lower tiles
 
 __host__ __device__ inline int sk_ns(int64_t I) { return (int)(((I + 15) / 16 + 1) / 2); }
 
-// ANYI (with V4): I need not be a multiple of 4 (the batched class); the
-// quad across row I - 1 is then read value by value.
-template <int PREC, int CH, bool V4, bool ANYI = false>
+// QUAD: I >= 4, any alignment of the rows.  MS: super tiles per wave (1 where
+// I <= SK_MS1_MAXI).
+//
+// What bounds it: the matrix cores with FP64 products (I = 160), the reading of Y
+// against the splitting of its values into bf16 parts with bf16x6 (I = 48).  48^5
+// in bf16x6 368 us (579), 160^4 in FP64 2.54 ms (2.94): with the selects beside
+// the loads every stage waited out its own loads before it was multiplied; with
+// the loader's tasks on the waves that multiply, the one came after the other; and
+// rows stored four apart met 4-way bank conflicts.
+template <int PREC, int CH, bool QUAD, int MS>
 __device__ __forceinline__ void gram_skinny_body(const float *__restrict__ Y, int I, int64_t P, int nkc, int kc,
                                                  double *__restrict__ partials) {
     constexpr int NQ = Frag<PREC>::NQ;
@@ -614,9 +625,9 @@ __device__ __forceinline__ void gram_skinny_body(const float *__restrict__ Y, in
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4;
     const int stage_q = CH * NQ * 4 * TBp;   // uint4 per stage buffer
 
-    int sbi[SK_MS], sbj[SK_MS];
+    int sbi[MS], sbj[MS];
 #pragma unroll
-    for (int m = 0; m < SK_MS; ++m) {
+    for (int m = 0; m < MS; ++m) {
         const int q = wave + SK_W * m;
         int bi = -1, bj = 0;
         if (q < NSS) {
@@ -627,10 +638,10 @@ __device__ __forceinline__ void gram_skinny_body(const float *__restrict__ Y, in
         sbi[m] = bi;
         sbj[m] = bj;
     }
-    AccT acc[SK_MS][2][2];
-    f64x4 acc64[SK_MS][2][2];
+    AccT acc[MS][2][2];
+    f64x4 acc64[MS][2][2];
 #pragma unroll
-    for (int m = 0; m < SK_MS; ++m)
+    for (int m = 0; m < MS; ++m)
 #pragma unroll
         for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -639,79 +650,65 @@ __device__ __forceinline__ void gram_skinny_body(const float *__restrict__ Y, in
                 acc64[m][x][y] = f64x4{0, 0, 0, 0};
             }
 
-    // V4 (I % 4 == 0, or any I with ANYI): task (row quad iq, group g, chunk c)
-    // loads the 4 x 8 block Y(4 iq .. 4 iq + 3, p0 + 32 c + 8 g + j) with eight
-    // 16-byte loads (consecutive lanes on consecutive row quads) and builds
-    // the four rows' fragments.  Otherwise task (row i, group g, chunk c)
-    // loads the 8 values of one row with 4-byte loads.
-    constexpr int RPT = V4 ? 4 : 1;                 // rows per task
-    constexpr int NTK = V4 ? 1 : SK_TASKS;          // tasks per thread
-    const int TQ = TBp / RPT;                       // row groups
+    // QUAD: task (row quad iq, group g, chunk c) loads the 4 x 8 block
+    // Y(4 iq .. 4 iq + 3, p0 + 32 c + 8 g + j) with eight 16-byte loads (consecutive
+    // lanes on consecutive row quads; the last quad of I % 4 != 0 rows is read from
+    // row I - 4 on) and builds the four rows' fragments.  Otherwise task
+    // (row i, group g, chunk c) loads the 8 values of one row with 4-byte loads.
+    constexpr int RPT = QUAD ? 4 : 1;               // rows per task
+    const int TQ = (I + RPT - 1) / RPT;             // row groups
     const int ntask = TQ * 4 * CH;
-    float raw[NTK][RPT][8];
+    // loader tasks start at the last wave, super tiles at the first: where there
+    // are fewer of both than waves, different waves load and multiply.  Rows from
+    // I on of a stage hold anything: they reach only outputs that are not read.
+    const int tk = SK_T - 64 - 64 * wave + lane;
+    const bool has_task = tk < ntask;   // one task per thread at most
+    const int iq = min(tk, ntask - 1) % TQ, rest = min(tk, ntask - 1) / TQ, gg = rest & 3, tc = rest >> 2;
+    const int row0 = QUAD ? min(4 * iq, I - 4) : iq;
+    const int col0 = 32 * tc + 8 * gg;
+    float raw[RPT][8];
+    // The loads alone, unmasked (columns from P on read column p0): a select here
+    // would wait for its load before the stage is multiplied.
     auto load = [&](int st) {
         const int64_t p0 = ((int64_t)st * nkc + kc) * 32 * CH;
 #pragma unroll
-        for (int u = 0; u < NTK; ++u) {
-            const int t = tid + SK_T * u;
-            const int iq = t % TQ, rest = t / TQ, gg = rest & 3, c = rest >> 2;
-            const bool ok = t < ntask && RPT * iq < I;
-            if (ANYI && RPT * iq + RPT > I) {
-                // the quad across row I - 1: its rows below I one at a time
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int64_t pp = p0 + 32 * c + 8 * gg + j;
-                    const bool in = ok && pp < P;
-                    const int64_t a = (int64_t)(ok ? RPT * iq : 0) + (int64_t)I * (in ? pp : p0);
-#pragma unroll
-                    for (int rr = 0; rr < RPT; ++rr) {
-                        const bool rin = in && RPT * iq + rr < I;
-                        raw[u][rr][j] = rin ? Y[a + (rin ? rr : 0)] : 0.f;
-                    }
-                }
-                continue;
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int64_t pp = p0 + 32 * c + 8 * gg + j;
-                const bool in = ok && pp < P;
-                const int64_t pc = in ? pp : p0;
-                const int64_t a = (int64_t)(ok ? RPT * iq : 0) + (int64_t)I * pc;
-                if constexpr (V4) {
-                    // 4-byte alignment suffices (ANYI: rows of any length)
-                    const f32x4u v = *reinterpret_cast<const f32x4u *>(Y + a);
-                    raw[u][0][j] = in ? v.x : 0.f;
-                    raw[u][1][j] = in ? v.y : 0.f;
-                    raw[u][2][j] = in ? v.z : 0.f;
-                    raw[u][3][j] = in ? v.w : 0.f;
-                } else {
-                    const float v = Y[a];
-                    raw[u][0][j] = in ? v : 0.f;
-                }
+        for (int j = 0; j < 8; ++j) {
+            const int64_t pp = p0 + col0 + j;
+            const int64_t a = row0 + (int64_t)I * (pp < P ? pp : p0);
+            if constexpr (QUAD) {
+                const f32x4u v = *reinterpret_cast<const f32x4u *>(Y + a);   // 4-byte alignment suffices
+                raw[0][j] = v.x;
+                raw[1][j] = v.y;
+                raw[2][j] = v.z;
+                raw[3][j] = v.w;
+            } else {
+                raw[0][j] = Y[a];
             }
         }
     };
-    auto store = [&](int buf) {
-        uint4 *sb = s_sk + (size_t)buf * stage_q;
+    auto store = [&](int st) {
+        if (!has_task) return;
+        uint4 *sb = s_sk + (size_t)(st & 1) * stage_q;
+        const int64_t left = P - ((int64_t)st * nkc + kc) * 32 * CH;   // columns of the stage within Y
+        if (left < 32 * CH) {
 #pragma unroll
-        for (int u = 0; u < NTK; ++u) {
-            const int t = tid + SK_T * u;
-            if (t < ntask) {
-                const int iq = t % TQ, rest = t / TQ, gg = rest & 3, c = rest >> 2;
+            for (int j = 0; j < 8; ++j)
 #pragma unroll
-                for (int rr = 0; rr < RPT; ++rr) {
-                    FragQ<PREC> f;
-                    make_frag(raw[u][rr], f.f);
+                for (int rr = 0; rr < RPT; ++rr)
+                    if (col0 + j >= left) raw[rr][j] = 0.f;
+        }
 #pragma unroll
-                    for (int qq = 0; qq < NQ; ++qq) sb[((c * NQ + qq) * 4 + gg) * TBp + RPT * iq + rr] = f.q[qq];
-                }
-            }
+        for (int rr = 0; rr < RPT; ++rr) {   // rows shared by the last two quads are stored twice, alike
+            FragQ<PREC> f;
+            make_frag(raw[rr], f.f);
+#pragma unroll
+            for (int qq = 0; qq < NQ; ++qq) sb[((tc * NQ + qq) * 4 + gg) * TBp + l1_row(row0 + rr)] = f.q[qq];
         }
     };
     auto frag = [&](const uint4 *sb, int c, int row, Frag<PREC> &f) {
         FragQ<PREC> t;
 #pragma unroll
-        for (int qq = 0; qq < NQ; ++qq) t.q[qq] = sb[((c * NQ + qq) * 4 + g) * TBp + row];
+        for (int qq = 0; qq < NQ; ++qq) t.q[qq] = sb[((c * NQ + qq) * 4 + g) * TBp + l1_row(row)];
         f = t.f;
     };
 
@@ -727,7 +724,7 @@ __device__ __forceinline__ void gram_skinny_body(const float *__restrict__ Y, in
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
 #pragma unroll
-            for (int m = 0; m < SK_MS; ++m) {
+            for (int m = 0; m < MS; ++m) {
                 if (sbi[m] < 0) continue;   // uniform within the wave
                 Frag<PREC> fa[2], fb[2];
 #pragma unroll
@@ -747,7 +744,7 @@ __device__ __forceinline__ void gram_skinny_body(const float *__restrict__ Y, in
             ++chunk;
             if (!F64ACC && chunk % GRAM_FLUSH == 0) {
 #pragma unroll
-                for (int m = 0; m < SK_MS; ++m)
+                for (int m = 0; m < MS; ++m)
 #pragma unroll
                     for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -758,12 +755,12 @@ __device__ __forceinline__ void gram_skinny_body(const float *__restrict__ Y, in
                         }
             }
         }
-        if (st + 1 < nst) store((st + 1) & 1);
+        if (st + 1 < nst) store(st + 1);
         __syncthreads();
     }
     // partial super tiles: element (il, jl) of super tile q at [(kc NSS + q) 1024 + il + 32 jl]
 #pragma unroll
-    for (int m = 0; m < SK_MS; ++m) {
+    for (int m = 0; m < MS; ++m) {
         if (sbi[m] < 0) continue;
         const int q = wave + SK_W * m;
         double *dst = partials + ((int64_t)kc * NSS + q) * 1024;
