@@ -175,7 +175,7 @@ static void plan_layout(sth_plan_s &pl) {
             maxUq = std::max(maxUq, std::max(ttm_prep_bytes(stp.I, stp.R, tp), ttm_prep_bytes(stp.R, stp.R, tp)));
             maxSmall = std::max(maxSmall, als_small_doubles(stp.I, stp.R) * sizeof(double));
             const int I = (int)stp.I, R = (int)stp.R;
-            maxGemm = std::max(maxGemm, gemm_tn_ws_bytes(R, R, I));
+            maxGemm = std::max({maxGemm, gemm_tn_ws_bytes(R, R, I), gemm_ws_bytes(R, R, I), gemm_ws_bytes(I, R, R), gemm_ws_bytes(R, R, R)});
         }
     }
     Arena a;
@@ -347,6 +347,14 @@ AlsBufs als_bufs(double *base, int64_t I, int64_t R) {
     return b;
 }
 
+// C = op(A) op(B) for the ALS branch, one of the operands transposed at most: by
+// the matrix cores for FP64 data, in LDS panels for FP32 data (see gemm_f64).
+hipError_t als_gemm(int dtype, int ta, int tb, int m, int n, int k, const double *A, int64_t lda, const double *B,
+                    int64_t ldb, double *C, int64_t ldc, void *ws, hipStream_t s) {
+    if (dtype != DT_F64) return gemm_f64(ta, tb, m, n, k, 1.0, A, lda, B, ldb, 0.0, C, ldc, ws, s);
+    return ta ? gemm_tn(m, n, k, A, lda, B, ldb, C, ldc, ws, s) : gemm_nn(tb != 0, m, n, k, A, lda, B, ldb, C, ldc, s);
+}
+
 // Shifted Cholesky-QR3 of the I x R matrix A: Q = A R^{-1} with R = R3 R2 R1
 // upper triangular with a positive diagonal.  The first pass factors
 // A^T A + s I (s = 11 (I R + R (R + 1)) u ||A||_F^2, u = 2^-53), which exists
@@ -356,22 +364,22 @@ AlsBufs als_bufs(double *base, int64_t I, int64_t R) {
 // 2^-k core of the 4-way workload) L_k has a condition number near 1e9,
 // beyond what plain Cholesky-QR twice tolerates.  Uses b.T1, b.P, b.G2 and
 // the R x R buffers; Q may alias nothing in A.
-hipError_t cholqr3(const double *A, int I, int R, double *Q, double *Rfac, AlsBufs &b, void *gws,
+hipError_t cholqr3(int dtype, const double *A, int I, int R, double *Q, double *Rfac, AlsBufs &b, void *gws,
                    int64_t *flag, hipStream_t s) {
     hipError_t e;
     const double shift = 11.0 * ((double)I * R + (double)R * (R + 1)) * 1.1102230246251565e-16 * R;
-    if ((e = gemm_tn(R, R, I, A, I, A, I, b.G2, R, gws, s))) return e;
+    if ((e = als_gemm(dtype, 1, 0, R, R, I, A, I, A, I, b.G2, R, gws, s))) return e;
     if ((e = chol_launch(b.G2, R, R, shift, b.R1, b.R1inv, flag, s))) return e;
-    if ((e = gemm_nn(false, I, R, R, A, I, b.R1inv, R, b.T1, I, s))) return e;
-    if ((e = gemm_tn(R, R, I, b.T1, I, b.T1, I, b.G2, R, gws, s))) return e;
+    if ((e = als_gemm(dtype, 0, 0, I, R, R, A, I, b.R1inv, R, b.T1, I, gws, s))) return e;
+    if ((e = als_gemm(dtype, 1, 0, R, R, I, b.T1, I, b.T1, I, b.G2, R, gws, s))) return e;
     if ((e = chol_launch(b.G2, R, R, 0.0, b.R2, b.R2inv, flag, s))) return e;
-    if ((e = gemm_nn(false, I, R, R, b.T1, I, b.R2inv, R, b.P, I, s))) return e;
-    if ((e = gemm_tn(R, R, I, b.P, I, b.P, I, b.G2, R, gws, s))) return e;
+    if ((e = als_gemm(dtype, 0, 0, I, R, R, b.T1, I, b.R2inv, R, b.P, I, gws, s))) return e;
+    if ((e = als_gemm(dtype, 1, 0, R, R, I, b.P, I, b.P, I, b.G2, R, gws, s))) return e;
     if ((e = chol_launch(b.G2, R, R, 0.0, b.Rc, b.Rcinv, flag, s))) return e;
-    if ((e = gemm_nn(false, I, R, R, b.P, I, b.Rcinv, R, Q, I, s))) return e;
+    if ((e = als_gemm(dtype, 0, 0, I, R, R, b.P, I, b.Rcinv, R, Q, I, gws, s))) return e;
     if (Rfac) {
-        if ((e = gemm_nn(false, R, R, R, b.R2, R, b.R1, R, b.C, R, s))) return e;
-        if ((e = gemm_nn(false, R, R, R, b.Rc, R, b.C, R, Rfac, R, s))) return e;
+        if ((e = als_gemm(dtype, 0, 0, R, R, R, b.R2, R, b.R1, R, b.C, R, gws, s))) return e;
+        if ((e = als_gemm(dtype, 0, 0, R, R, R, b.Rc, R, b.C, R, Rfac, R, gws, s))) return e;
     }
     return hipSuccess;
 }
@@ -410,7 +418,7 @@ static sth_status exec_step(const sth_plan_s &pl, const Step &stp, const void *s
         HIPCHK(gaussian_f64(b.L0, (int64_t)I * R, seed, (uint64_t)n, s), "als init");
         L0 = b.L0;
     }
-    HIPCHK(cholqr3(L0, I, R, b.Q, nullptr, b, gws, flag, s), "als qr0");
+    HIPCHK(cholqr3(p->dtype, L0, I, R, b.Q, nullptr, b, gws, flag, s), "als qr0");
     for (int k = 0; k < p->als_iters; ++k) {
         // Z = Y x_n Q^T  (R_k as a tensor)
         HIPCHK(ttm_prep_u(b.Q, I, R, 0, tp, uq, s), "als prep");
@@ -418,13 +426,13 @@ static sth_status exec_step(const sth_plan_s &pl, const Step &stp, const void *s
         // P = Y_(n) Z_(n)^T  (TTT)
         HIPCHK(gram_launch(p->dtype, gp, src, bufZ, stp.L, I, R, stp.M, false, part, b.P, s), "als ttt");
         // C = R_k^T R_k = Q^T P ;  L_{k+1} = P C^{-1}
-        HIPCHK(gemm_tn(R, R, I, b.Q, I, b.P, I, b.C, R, gws, s), "als C");
+        HIPCHK(als_gemm(p->dtype, 1, 0, R, R, I, b.Q, I, b.P, I, b.C, R, gws, s), "als C");
         HIPCHK(chol_launch(b.C, R, R, 0.0, b.Rc, b.Rcinv, flag, s), "als chol");
-        HIPCHK(gemm_nn(false, I, R, R, b.P, I, b.Rcinv, R, b.T1, I, s), "als L1");
-        HIPCHK(gemm_nn(true, I, R, R, b.T1, I, b.Rcinv, R, b.Lk, I, s), "als L2");
+        HIPCHK(als_gemm(p->dtype, 0, 0, I, R, R, b.P, I, b.Rcinv, R, b.T1, I, gws, s), "als L1");
+        HIPCHK(als_gemm(p->dtype, 0, 1, I, R, R, b.T1, I, b.Rcinv, R, b.Lk, I, gws, s), "als L2");
         const bool last = (k + 1 == p->als_iters);
         // next basis, or the final Q^ R^ = L
-        HIPCHK(cholqr3(b.Lk, I, R, last ? Un : b.Q, last ? b.Rhat : nullptr, b, gws, flag, s), "als qr");
+        HIPCHK(cholqr3(p->dtype, b.Lk, I, R, last ? Un : b.Q, last ? b.Rhat : nullptr, b, gws, flag, s), "als qr");
     }
     // core update: Y' = R x_n R^  (Z'(a, r, b) = sum_s R^(r, s) Z(a, s, b))
     HIPCHK(ttm_prep_u(b.Rhat, R, R, 1, tp, uq, s), "als core prep");

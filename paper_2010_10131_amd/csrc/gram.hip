@@ -360,8 +360,10 @@ hipError_t launch_gram_t(const T *A, const T *B, int64_t L, int64_t IA, int64_t 
             return hipGetLastError();
         }
     }
-    if constexpr (!SYM && PREC == P_FP64 && WT == 4) {
-        // rows beyond one block and few columns of B
+    if constexpr (!SYM && sizeof(T) == 8 && WT == 4) {
+        // rows beyond one block and few columns of B; FP32 data keeps the block
+        // kernel's order of operations (its ALS sweeps round the bases to the
+        // next product's factors and carry a last-bit difference on)
         if (L == 1 && IA >= 2 && IB <= 64) {
             if (IB <= 16) return launch_ttt_narrow<T, 1>(A, B, IA, IB, P, g, partials, S, s);
             if (IB <= 32) return launch_ttt_narrow<T, 2>(A, B, IA, IB, P, g, partials, S, s);

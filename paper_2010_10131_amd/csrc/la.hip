@@ -4,6 +4,7 @@
 //   gemm_tn       C = A^T B over a long contraction, split over workgroups
 //                 with a fixed-order reduction (deterministic)
 //   gemm_nn       C = A op(B) with a short contraction
+//   gemm_f64      C = alpha op(A) op(B) + beta C in LDS panels (FP32 data)
 //   chol_kernel   one workgroup: G (+ shift) = R^T R (Cholesky, R upper),
 //                 writes R and R^{-1}; used for the normal equations of
 //                 Alg. 3 and for Cholesky-QR
@@ -156,6 +157,140 @@ hipError_t gemm_nn(bool tb, int m, int n, int k, const double *A, int64_t lda, c
     return hipGetLastError();
 }
 
+// The LDS-panel products, for the ALS branch on FP32 data.  There the bases are
+// rounded to the FP32 or bf16 factors of the next product, and the sweeps carry a
+// last-bit difference on: one element rounded the other way moves the factors by
+// 1e-8 to 1e-7.  These keep the order of operations that the results of FP32 data
+// have had; FP64 data takes gemm_tn and gemm_nn (5 us a call for 34).
+constexpr int GT = 32;   // gemm tile (rows and columns of C)
+constexpr int GK = 128;  // k-extent staged in LDS per step
+
+// C_part[z] (m x n, ldc) = op(A) op(B) over k-slice z.  The skinny products
+// of the eigensolver and the ALS branch are latency-bound, so every step
+// loads a whole GT x GK panel of each operand with all loads in flight at
+// once (coalesced along the contiguous index of each operand), then runs
+// GK rank-1 updates from LDS: one global round trip per 128 values of k.
+__global__ __launch_bounds__(256) void gemm_f64_kernel(int ta, int tb, int m, int n, int k,
+                                                       double alpha, const double *__restrict__ A,
+                                                       int64_t lda, const double *__restrict__ B,
+                                                       int64_t ldb, double beta, double *__restrict__ C,
+                                                       int64_t ldc, int kslice, double *__restrict__ part) {
+    extern __shared__ __align__(16) double s_gemm[];
+    double *sA = s_gemm;                  // sA[kk * (GT + 1) + r] = op(A)(row0 + r, kc + kk)
+    double *sB = s_gemm + GK * (GT + 1);  // sB[kk * (GT + 1) + c] = op(B)(kc + kk, col0 + c)
+    constexpr int PER = GT * GK / 256;    // elements of each panel per thread
+    const int tid = threadIdx.x;
+    const int tx = tid % 16, ty = tid / 16;
+    const int row0 = blockIdx.x * GT, col0 = blockIdx.y * GT;
+    const int kz = blockIdx.z;
+    const int kbeg = kz * kslice, kend = min(k, kbeg + kslice);
+    double acc[2][2] = {{0, 0}, {0, 0}};
+    for (int kc = kbeg; kc < kend; kc += GK) {
+        double ra[PER], rb[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int e = tid + 256 * u;
+            // A panel: contiguous along r (op = A) or along kk (op = A^T)
+            int r, kk;
+            if (ta) { kk = e % GK; r = e / GK; } else { r = e % GT; kk = e / GT; }
+            int gr = row0 + r, gk = kc + kk;
+            ra[u] = (gr < m && gk < kend) ? (ta ? A[gk + lda * gr] : A[gr + lda * gk]) : 0.0;
+            // B panel: contiguous along kk (op = B) or along c (op = B^T)
+            int cc, kb;
+            if (tb) { cc = e % GT; kb = e / GT; } else { kb = e % GK; cc = e / GK; }
+            int gc = col0 + cc, gk2 = kc + kb;
+            rb[u] = (gc < n && gk2 < kend) ? (tb ? B[gc + ldb * gk2] : B[gk2 + ldb * gc]) : 0.0;
+        }
+        __syncthreads();  // the previous step's reads of the panels are done
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int e = tid + 256 * u;
+            int r, kk;
+            if (ta) { kk = e % GK; r = e / GK; } else { r = e % GT; kk = e / GT; }
+            sA[kk * (GT + 1) + r] = ra[u];
+            int cc, kb;
+            if (tb) { cc = e % GT; kb = e / GT; } else { kb = e % GK; cc = e / GK; }
+            sB[kb * (GT + 1) + cc] = rb[u];
+        }
+        __syncthreads();
+        const int kn = min(GK, kend - kc);
+#pragma unroll 8
+        for (int kk = 0; kk < kn; ++kk) {
+            const double a0 = sA[kk * (GT + 1) + tx], a1 = sA[kk * (GT + 1) + tx + 16];
+            const double b0 = sB[kk * (GT + 1) + ty], b1 = sB[kk * (GT + 1) + ty + 16];
+            acc[0][0] += a0 * b0;
+            acc[1][0] += a1 * b0;
+            acc[0][1] += a0 * b1;
+            acc[1][1] += a1 * b1;
+        }
+    }
+    for (int x = 0; x < 2; ++x)
+        for (int y = 0; y < 2; ++y) {
+            int r = row0 + tx + 16 * x, c = col0 + ty + 16 * y;
+            if (r < m && c < n) {
+                if (part) {
+                    part[(int64_t)kz * m * n + r + (int64_t)m * c] = acc[x][y];
+                } else {
+                    double old = (beta != 0.0) ? C[r + ldc * c] : 0.0;
+                    C[r + ldc * c] = alpha * acc[x][y] + beta * old;
+                }
+            }
+        }
+}
+
+constexpr size_t GEMM_LDS = (size_t)2 * GK * (GT + 1) * sizeof(double);
+
+__global__ void gemm_f64_reduce_kernel(int m, int n, int nz, const double *__restrict__ part,
+                                   double alpha, double beta, double *__restrict__ C, int64_t ldc) {
+    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= (int64_t)m * n) return;
+    int r = (int)(e % m), c = (int)(e / m);
+    double s = 0.0;
+    for (int z = 0; z < nz; ++z) s += part[(int64_t)z * m * n + e];
+    double old = (beta != 0.0) ? C[r + ldc * c] : 0.0;
+    C[r + ldc * c] = alpha * s + beta * old;
+}
+
+size_t gemm_ws_bytes(int m, int n, int k) {
+    int nz = gemm_splits(m, n, k);
+    return nz > 1 ? (size_t)nz * m * n * sizeof(double) : 0;
+}
+
+// k-slices: one LDS step (GK values of k) per workgroup where the tile count
+// leaves the chip idle, at most 32 slices.
+int gemm_splits(int m, int n, int k) {
+    const int tiles = ((m + GT - 1) / GT) * ((n + GT - 1) / GT);
+    if (tiles >= 256) return 1;
+    int nz = (k + GK - 1) / GK;
+    nz = std::min(nz, 32);
+    while (nz > 1 && tiles * nz > 1024) nz = (nz + 1) / 2;
+    return std::max(nz, 1);
+}
+
+hipError_t gemm_f64(int ta, int tb, int m, int n, int k, double alpha, const double *A,
+                    int64_t lda, const double *B, int64_t ldb, double beta, double *C, int64_t ldc,
+                    void *ws, hipStream_t s) {
+    if (m == 0 || n == 0) return hipSuccess;
+    int nz = gemm_splits(m, n, k);
+    int kslice = (k + nz - 1) / nz;
+    kslice = (kslice + GT - 1) / GT * GT;
+    if (kslice == 0) kslice = GT;
+    nz = std::max(1, (k + kslice - 1) / kslice);
+    dim3 grid((m + GT - 1) / GT, (n + GT - 1) / GT, nz);
+    double *part = nz > 1 ? (double *)ws : nullptr;
+    hipError_t ea = hipFuncSetAttribute((const void *)gemm_f64_kernel,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)GEMM_LDS);
+    if (ea != hipSuccess) return ea;
+    hipLaunchKernelGGL(gemm_f64_kernel, grid, dim3(256), GEMM_LDS, s, ta, tb, m, n, k, alpha, A, lda, B,
+                       ldb, beta, C, ldc, kslice, part);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || nz == 1) return e;
+    int64_t tot = (int64_t)m * n;
+    hipLaunchKernelGGL(gemm_f64_reduce_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, m,
+                       n, nz, part, alpha, beta, C, ldc);
+    return hipGetLastError();
+}
+
 constexpr int CHOL_THREADS = 512;
 
 __global__ __launch_bounds__(CHOL_THREADS) void chol_kernel(const double *__restrict__ G, int n,
@@ -163,7 +298,7 @@ __global__ __launch_bounds__(CHOL_THREADS) void chol_kernel(const double *__rest
                                                             double *__restrict__ Rout,
                                                             double *__restrict__ Rinv,
                                                             int64_t *__restrict__ flag) {
-    chol_body<CHOL_THREADS>(G, n, ldg, shift_rel, Rout, Rinv, flag);
+    chol_body<CHOL_THREADS, true>(G, n, ldg, shift_rel, Rout, Rinv, flag);
 }
 
 hipError_t chol_launch(const double *G, int n, int64_t ldg, double shift_rel, double *R,
