@@ -67,6 +67,222 @@ __global__ __launch_bounds__(SK_T) void gram_skinny_kernel(const float *__restri
     gram_skinny_body<PREC, CH, QUAD, MS>(Y, I, P, nkc, blockIdx.x, partials);
 }
 
+// ---- FP64 products, I <= 160: the lower triangle in 16 x 16 tiles -----------
+// One workgroup per CU walks row blocks of SC rows (dealt round-robin, so that
+// the chip streams one region), staged in LDS as they are in memory: i fastest
+// when L = 1 (one contiguous run), each column's SC rows otherwise.  The waves
+// share the 32 x 32 super tiles of the lower triangle (two of 16 x 16 a side, the
+// upper one of a diagonal super tile left out), MS each at most; where there are
+// fewer than waves, ks groups of waves split a block's rows and are summed at the
+// end.  Two stages of loads are in flight.  Float data is widened as it is stored (widened as it is read, once per
+// tile and step, 160^4's first mode took 3.2 ms: the conversions and the products
+// share the FP64 units).
+//
+// Bound by the FP64 matrix cores (64 cycles a 16 x 16 x 4 product).  160^4 with
+// 160 of 4.1 M rows: 2.20 ms (1.6 ms of products), 2.45 in the skinny body, whose
+// loading waves widen and sort fragments beside their products.  The later modes,
+// I = 160 with L = 16, 256, ..: 289 us, 967 in 128 x 128 blocks, which pad the
+// triangle of 55 tiles to 160.  64^3 double: 8 us a mode, 20 in one block of 64
+// and few workgroups.
+constexpr int TRI_T = 512, TRI_W = TRI_T / 64;
+constexpr int TRI_SC = 32;
+constexpr int TRI_MAXI = 160;   // 15 super tiles: two per wave
+
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
+// doubles of a stage (even; reads of the rows beyond I stay within)
+__host__ __device__ inline int tri_stage(int I, bool flat) {
+    return flat ? (I * TRI_SC + 34) / 2 * 2 : 32 * ((I + 31) / 32) * (TRI_SC + 2);
+}
+
+template <typename T, int MS, bool FLAT>
+__global__ __launch_bounds__(TRI_T) void gram_tri64_kernel(const T *__restrict__ Y, int64_t L, int I, int64_t P,
+                                                          int ks, int nkc, double *__restrict__ partials) {
+    constexpr int VE = 16 / sizeof(T);
+    constexpr int NV = (TRI_MAXI * TRI_SC / VE + TRI_T - 1) / TRI_T;   // 16-byte vectors per thread and stage
+    constexpr int SC = TRI_SC, LDP = SC + 2;
+    typedef T vec_t __attribute__((ext_vector_type(VE)));
+    extern __shared__ __align__(16) char s_tri[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tr = lane & 15, tg = lane >> 4;
+    const int ns = ((I + 15) / 16 + 1) / 2, nss = ns * (ns + 1) / 2, noff = nss - ns;
+    const int gw = TRI_W / ks, wg = wave % gw, gk = wave / gw;   // wave of its group, group
+    // element (row i, k of the stage) at i * rs + k * cs
+    const int rs = FLAT ? 1 : LDP, cs = FLAT ? I : 1;
+    const int stage_e = tri_stage(I, FLAT);
+    double *s_st = reinterpret_cast<double *>(s_tri);
+
+    // super tiles off the diagonal first (four products a step), then those on it
+    // (three), dealt to the SIMDs (wave mod 4) in turn; -1: none
+    int q[MS], oa[MS], ob[MS];
+    bool diag[MS];
+#pragma unroll
+    for (int m = 0; m < MS; ++m) {
+        const int u = gw >= 4 ? (wg & 3) + 4 * ((wg >> 2) + (gw >> 2) * m) : wg + gw * m;
+        int bi = 0, bj = 0;
+        diag[m] = u >= noff;
+        if (u < noff) {   // (1, 0), (2, 0), (2, 1), ..
+            bi = 1;
+            while (bi * (bi + 1) / 2 <= u) ++bi;
+            bj = u - bi * (bi - 1) / 2;
+        } else if (u < nss) {
+            bi = bj = u - noff;
+        }
+        q[m] = u < nss ? bi * (bi + 1) / 2 + bj : -1;
+        oa[m] = (32 * bi + tr) * rs + tg * cs;
+        ob[m] = (32 * bj + tr) * rs + tg * cs;
+    }
+    f64x4 acc[MS][2][2];
+#pragma unroll
+    for (int m = 0; m < MS; ++m)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[m][x >> 1][x & 1] = f64x4{0.0, 0.0, 0.0, 0.0};
+
+    const int64_t nblk = (P + SC - 1) / SC;
+    const int kc = blockIdx.x;
+    const int nst = kc < nblk ? (int)((nblk - 1 - kc) / nkc + 1) : 0;
+    // L > 1: this thread's rows p of a block (the same for all its vectors) and
+    // their place in the tensor, carried from stage to stage
+    const int vr = SC / VE, pv = VE * (tid % vr), row0 = tid / vr, rstep = TRI_T / vr;
+    const int64_t step = (int64_t)SC * nkc, qs = FLAT ? 0 : step / L, r_s = FLAT ? 0 : step - qs * L;
+    int64_t pb = 0, pa = 0;
+    if (!FLAT) {
+        const int64_t p = (int64_t)kc * SC + pv;
+        pb = p / L;
+        pa = p - pb * L;
+    }
+    vec_t raws[2][NV];   // two stages in flight
+    // the loads alone, unmasked and unconditional (clamped places): a branch or a
+    // select here would wait for them before the stage in hand is multiplied
+    const int64_t count = P * I;
+    auto load = [&](int st, vec_t (&raw)[NV]) {
+        const int64_t p0 = ((int64_t)st * nkc + kc) * SC;
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+            if constexpr (FLAT) {
+                const int64_t e = p0 * I + VE * (tid + TRI_T * u);
+                __builtin_memcpy(&raw[u], Y + min(e, count - VE), 16);
+            } else {
+                const int row = min(row0 + rstep * u, I - 1);
+                __builtin_memcpy(&raw[u], Y + L * row + (p0 + pv < P ? pa + L * I * pb : 0), 16);
+            }
+        }
+        if constexpr (!FLAT) {
+            pa += r_s;
+            pb += qs;
+            if (pa >= L) {
+                pa -= L;
+                ++pb;
+            }
+        }
+    };
+    auto store = [&](int st, vec_t (&raw)[NV]) {
+        const int64_t p0 = ((int64_t)st * nkc + kc) * SC;
+        double *d = s_st + (st & 1) * stage_e;
+        if (p0 + SC > P) {   // the last block of rows: zeroes past the end
+#pragma unroll
+            for (int u = 0; u < NV; ++u)
+#pragma unroll
+                for (int c = 0; c < VE; ++c) {
+                    if constexpr (FLAT) {
+                        const int64_t e = p0 * I + VE * (tid + TRI_T * u) + c;
+                        raw[u][c] = e < count ? Y[e] : (T)0;
+                    } else if (p0 + pv >= P) raw[u][c] = (T)0;
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+            const int e = VE * (tid + TRI_T * u), row = row0 + rstep * u;
+            if (FLAT ? e < I * SC : row < I) {
+                double *x = d + (FLAT ? e : row * LDP + pv);
+#pragma unroll
+                for (int c = 0; c < VE; c += 2)
+                    *reinterpret_cast<f64x2 *>(x + c) = f64x2{(double)raw[u][c], (double)raw[u][c + 1]};
+            }
+        }
+    };
+    auto compute = [&](int st) {
+        const double *d = s_st + (st & 1) * stage_e;
+        // the next step's elements are read while one is multiplied
+        double a[2][MS][2], b[2][MS][2];
+        auto read = [&](int k, double (&x)[MS][2], double (&y)[MS][2]) {
+#pragma unroll
+            for (int m = 0; m < MS; ++m)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    x[m][h] = d[oa[m] + 16 * h * rs + k * cs];
+                    y[m][h] = d[ob[m] + 16 * h * rs + k * cs];
+                }
+        };
+        auto mult = [&](const double (&x)[MS][2], const double (&y)[MS][2]) {
+#pragma unroll
+            for (int m = 0; m < MS; ++m) {
+                if (q[m] < 0) continue;
+                acc[m][0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[m][0], y[m][0], acc[m][0][0], 0, 0, 0);
+                acc[m][1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[m][1], y[m][0], acc[m][1][0], 0, 0, 0);
+                acc[m][1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[m][1], y[m][1], acc[m][1][1], 0, 0, 0);
+                if (!diag[m]) acc[m][0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[m][0], y[m][1], acc[m][0][1], 0, 0, 0);
+            }
+        };
+        const int dk = 4 * ks;
+        read(4 * gk, a[0], b[0]);
+        int k = 4 * gk;
+        for (; k + dk < SC; k += 2 * dk) {
+            read(k + dk, a[1], b[1]);
+            mult(a[0], b[0]);
+            read(min(k + 2 * dk, SC - 4), a[0], b[0]);
+            mult(a[1], b[1]);
+        }
+        if (k < SC) mult(a[0], b[0]);
+    };
+    if (nst > 0) {
+        load(0, raws[0]);
+        load(1, raws[1]);
+        store(0, raws[0]);
+    }
+    __syncthreads();
+    for (int st = 0; st < nst; st += 2) {
+        load(st + 2, raws[0]);
+        compute(st);
+        if (st + 1 < nst) store(st + 1, raws[1]);
+        __syncthreads();
+        if (st + 1 >= nst) break;
+        load(st + 3, raws[1]);
+        compute(st + 1);
+        if (st + 2 < nst) store(st + 2, raws[0]);
+        __syncthreads();
+    }
+    if (ks > 1) {   // the groups' sums, in a fixed order
+        f64x4 *s_acc = reinterpret_cast<f64x4 *>(s_tri);
+        auto at = [&](int g, int m, int x) { return (((g * gw + wg) * MS + m) * 4 + x) * 64 + lane; };
+        if (gk > 0) {
+#pragma unroll
+            for (int m = 0; m < MS; ++m)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) s_acc[at(gk - 1, m, x)] = acc[m][x >> 1][x & 1];
+        }
+        __syncthreads();
+        if (gk > 0) return;
+        for (int g = 0; g < ks - 1; ++g)
+#pragma unroll
+            for (int m = 0; m < MS; ++m)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) acc[m][x >> 1][x & 1] += s_acc[at(g, m, x)];
+    }
+    // partial super tiles, summed by gram_reduce_kernel<32, true>
+#pragma unroll
+    for (int m = 0; m < MS; ++m) {
+        if (q[m] < 0) continue;
+        double *dst = partials + ((int64_t)kc * nss + q[m]) * 1024;
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) dst[16 * x + tg + 4 * v + 32 * (16 * y + tr)] = acc[m][x][y][v];
+    }
+}
+
 // Sums the partial blocks over the row ranges and writes the IA x IB result
 // (mirroring the lower triangle when SYM).  64 elements per workgroup, each
 // summed by four waves over interleaved ranges of partials (8 loads in
@@ -343,6 +559,58 @@ hipError_t launch_ttt_narrow(const T *A, const T *B, int64_t IA, int64_t IB, int
     return hipGetLastError();
 }
 
+// Geometry of the triangle kernel: rows per stage (two stages within the LDS and
+// a thread's vectors), wave groups along the contraction (the fewest products per
+// wave, then the fewest groups), workgroups: one per CU with at least two stages
+// each.
+struct TriShape {
+    int ks, ms, nkc;   // wave groups, super tiles per wave, workgroups
+    size_t lds;
+};
+
+int tri_nkc(int64_t P) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(device_cu_count(), P / (2 * TRI_SC)));
+}
+
+TriShape tri_shape(int64_t I, int64_t P, bool flat) {
+    TriShape t;
+    const int ns = sk_ns(I), nss = ns * (ns + 1) / 2;
+    double best = 1e9;
+    for (int ks = 1; ks <= TRI_W; ks *= 2) {
+        const int per = (nss + TRI_W / ks - 1) / (TRI_W / ks);
+        if (per <= 2 && (double)per / ks < best) {
+            best = (double)per / ks;
+            t.ks = ks;
+            t.ms = per;
+        }
+    }
+    t.lds = std::max((size_t)2 * tri_stage((int)I, flat) * sizeof(double),
+                     (size_t)(t.ks - 1) * (TRI_W / t.ks) * t.ms * 4 * 64 * sizeof(f64x4));
+    t.nkc = tri_nkc(P);
+    return t;
+}
+
+template <typename T, int MS>
+hipError_t launch_tri_m(const T *A, int64_t L, int64_t I, int64_t P, const TriShape &t, double *partials, hipStream_t s) {
+    auto kern = L == 1 ? gram_tri64_kernel<T, MS, true> : gram_tri64_kernel<T, MS, false>;
+    if (t.lds > 64 * 1024)
+        if (hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)t.lds)) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)t.nkc), dim3(TRI_T), t.lds, s, A, L, (int)I, P, t.ks, t.nkc, partials);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_tri(const T *A, int64_t L, int64_t I, int64_t M, double *partials, double *S, hipStream_t s) {
+    const TriShape t = tri_shape(I, L * M, L == 1);
+    hipError_t e = t.ms == 1 ? launch_tri_m<T, 1>(A, L, I, L * M, t, partials, s)
+                             : launch_tri_m<T, 2>(A, L, I, L * M, t, partials, s);
+    if (e != hipSuccess) return e;
+    const int ns = sk_ns(I);
+    hipLaunchKernelGGL((gram_reduce_kernel<32, true>), dim3(16, ns * (ns + 1) / 2), dim3(256), 0, s, partials, t.nkc, ns,
+                       ns * (ns + 1) / 2, I, I, S);
+    return hipGetLastError();
+}
+
 template <typename T, int PREC, int WT, bool SYM>
 hipError_t launch_gram_t(const T *A, const T *B, int64_t L, int64_t IA, int64_t IB, int64_t M,
                          const GramShape &g, double *partials, double *S, hipStream_t s) {
@@ -350,8 +618,14 @@ hipError_t launch_gram_t(const T *A, const T *B, int64_t L, int64_t IA, int64_t 
     const int64_t P = L * M;
     const int64_t total = (int64_t)g.nkc * g.nblocks;
     const int64_t per_xcd = (total + 7) / 8;
+    if constexpr (SYM && PREC == P_FP64) {
+        // whole 16-byte vectors along the rows; other L stay with the general kernel
+        if (IA <= TRI_MAXI && IA * P >= 64 && (L == 1 || L % (16 / (int64_t)sizeof(T)) == 0)) return launch_tri<T>(A, L, IA, M, partials, S, s);
+    }
     if constexpr (SYM && sizeof(T) == 4) {
-        if (L == 1 && IA <= SK_MAXI) return launch_skinny<PREC>(A, IA, M, partials, S, s);
+        if constexpr (PREC != P_FP64) {
+            if (L == 1 && IA <= SK_MAXI) return launch_skinny<PREC>(A, IA, M, partials, S, s);
+        }
         if (L == 1 && WT >= 2) {
             hipError_t e = launch_gram_l1<PREC, WT>(A, IA, M, g, partials, s);
             if (e != hipSuccess) return e;
@@ -427,11 +701,11 @@ size_t gram_ws_bytes(int64_t IA, int64_t IB, int64_t P, bool sym) {
     GramShape g = gram_shape(IA, IB, P, sym);
     size_t b = (size_t)g.nkc * g.nblocks * g.tb * g.tb * sizeof(double);
     if (sym && IA <= SK_MAXI) {
-        // the skinny path (L = 1; any precision)
+        // the skinny path (L = 1) and the triangle kernel (FP64 products)
         const int NS = sk_ns(IA);
-        for (int prec = P_FP64; prec <= P_BF16X6; ++prec)
-            for (int v4 = 0; v4 < 2; ++v4)
-                b = std::max(b, (size_t)sk_shape(prec, IA, P).nkc * (NS * (NS + 1) / 2) * 1024 * sizeof(double));
+        int nkc = IA <= TRI_MAXI ? tri_nkc(P) : 1;
+        for (int prec = P_FP32; prec <= P_BF16X6; ++prec) nkc = std::max(nkc, sk_shape(prec, IA, P).nkc);
+        b = std::max(b, (size_t)nkc * (NS * (NS + 1) / 2) * 1024 * sizeof(double));
     }
     return b;
 }

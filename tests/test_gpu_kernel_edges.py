@@ -181,23 +181,24 @@ def test_subspace_iteration_orders(api, n, R):
     assert np.all(U[top, np.arange(R)] > 0)
 
 
-@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3", "bf16x6"])
-@pytest.mark.parametrize("dims,n", [((1, 700), 0), ((3, 65), 0), ((4, 33), 0), ((5, 1000), 0), ((33, 129), 0),
+@pytest.mark.parametrize("prec", ["f64", "fp64", "fp32", "bf16x3", "bf16x6"])
+@pytest.mark.parametrize("dims,n", [((5, 3), 0), ((1, 700), 0), ((3, 65), 0), ((4, 33), 0), ((5, 1000), 0), ((33, 129), 0),
                                     ((96, 4100), 0), ((97, 515), 0), ((130, 301), 0), ((159, 2050), 0), ((160, 31), 0),
                                     ((161, 700), 0), ((163, 97), 0), ((256, 545), 0), ((258, 33), 0),
                                     ((7, 130, 5), 1), ((8, 33, 12), 1), ((9, 65, 40), 1), ((40, 129, 3), 1),
-                                    ((31, 20, 17), 1), ((1, 200, 9), 1), ((24, 257), 1)])
+                                    ((31, 20, 17), 1), ((1, 200, 9), 1), ((24, 257), 1), ((36, 150, 40), 1),
+                                    ((2, 65, 33), 1), ((6, 64, 64), 1)])
 def test_gram_edges(api, dims, n, prec):
     """Grams at the edges of their tiles, stages and loaders: rows and columns
     beyond whole quads, octets across fibres, a last chunk that is not full.  FP32 accumulates 128 products at most
     (128 eps32 of the sum of magnitudes, doubled), bf16x3 drops products below
     2^-16, FP64 stays within K eps."""
     rng = np.random.default_rng(sum(dims) + n)
-    X = np.asfortranarray(rng.standard_normal(dims).astype(np.float32))
+    X = np.asfortranarray(rng.standard_normal(dims).astype(np.float64 if prec == "f64" else np.float32))
     Xd = api.to_device(X)
-    S = api.to_numpy(api.gram_mode_n(Xd, n, prec))
+    S = api.to_numpy(api.gram_mode_n(Xd, n, "fp64" if prec == "f64" else prec))
     M = np.moveaxis(X.astype(np.float64), n, 0).reshape(dims[n], -1)
-    c = {"fp64": 4 * M.shape[1] * 2.2e-16, "fp32": 256 * 2.0 ** -24, "bf16x6": 256 * 2.0 ** -24,
+    c = {"f64": 4 * M.shape[1] * 2.2e-16, "fp64": 4 * M.shape[1] * 2.2e-16, "fp32": 256 * 2.0 ** -24, "bf16x6": 256 * 2.0 ** -24,
          "bf16x3": 256 * 2.0 ** -24 + 4 * 2.0 ** -16}[prec]
     assert np.all(np.abs(S - M @ M.T) <= c * (np.abs(M) @ np.abs(M).T))
     np.testing.assert_array_equal(S, S.T)
