@@ -26,9 +26,9 @@ namespace sth {
 //     the matrix cores.  W(B, J) (J <= K) lies where L(B, J) was.  The first wave
 //     updates the next diagonal block and goes on to factor it while the others
 //     do the rest: two barriers per panel.
-// Writes R = L^T (upper) and Rinv = L^{-T} (upper), n x n, tile by tile as they
-// become final; either may be NULL.  L^{-1} is left in LDS (lower tiles; the
-// upper ones hold other things).  A non-positive pivot sets flag[0] = 2 and is
+// L^{-1} is left in LDS (lower tiles; the upper ones hold other things); with
+// SWEEP (below) R = L^T (upper, may be NULL) and Rinv = L^{-T} (upper) are written,
+// n x n.  A non-positive pivot sets flag[0] = 2 and is
 // replaced by a tiny positive one so that the run continues.
 //
 // Bound by the serial chain of the diagonal blocks.  Against the form with lane
@@ -127,12 +127,14 @@ __device__ __forceinline__ void chol_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// SWEEP (the batched eigensolver): L^{-1} from L afterwards, block column by block
-// column from the last one, L^{-1}(B, K) = -(sum_{J in (K, B]} L^{-1}(B, J) L(J, K)) D_K^{-1}.
+// SWEEP (the batched eigensolver and the ALS branch): L^{-1} from L afterwards,
+// block column by block column from the last one,
+// L^{-1}(B, K) = -(sum_{J in (K, B]} L^{-1}(B, J) L(J, K)) D_K^{-1}.
 // Where a mode keeps more vectors than the product of the other ranks gives its
 // unfolding signal, the surplus eigenvectors lie in the noise, and which ones come
-// out hangs on the last bits of L^{-1}; the batch keeps the order of operations
-// that its results have had.  Order 80: 22 us in place of 15.
+// out hangs on the last bits of L^{-1}; ALS sweeps on FP32 data carry such bits on.
+// Both keep the order of operations that their results have had.  Order 80: 22 us
+// in place of 15.
 template <int NTH, bool SWEEP = false>
 __device__ __forceinline__ void chol_body(const double *__restrict__ G, int n, int64_t ldg,
                                           double shift_rel, double *__restrict__ Rout,
@@ -184,11 +186,10 @@ __device__ __forceinline__ void chol_body(const double *__restrict__ G, int n, i
 #pragma unroll
         for (int v = 0; v < 4; ++v) s_l[ident + cr + 4 * v] = tg + 4 * v == tr ? 1.0 : 0.0;
     } else {
-        // the triangles outside R and Rinv, but for the diagonal blocks
+        // the triangle outside R, but for the diagonal blocks
         for (int j = wave - 1; j < n; j += NW - 1)
             for (int i = (j / CB + 1) * CB + lane; i < n; i += 64) {
-                if (Rout) Rout[i + n * j] = 0.0;
-                if (Rinv && !SWEEP) Rinv[i + n * j] = 0.0;
+                if (SWEEP && Rout) Rout[i + n * j] = 0.0;
             }
     }
     // tile c -= P(b) X (c begun as 0 where fresh): X(k, j) = x[XK k + XJ j]
@@ -240,7 +241,7 @@ __device__ __forceinline__ void chol_body(const double *__restrict__ G, int n, i
 #pragma unroll
                 for (int c = 0; c < CB; ++c) dk[c + CLD * tr] = c >= tr ? a[c] : 0.0;
             }
-            if (Rout && tg == 0 && k0 + tr < n) {
+            if (SWEEP && Rout && tg == 0 && k0 + tr < n) {
 #pragma unroll
                 for (int c = 0; c < CB; ++c)
                     if (k0 + c < n) Rout[k0 + c + n * (k0 + tr)] = c <= tr ? a[c] : 0.0;
@@ -262,11 +263,6 @@ __device__ __forceinline__ void chol_body(const double *__restrict__ G, int n, i
             }
         }
         chol_sync();
-        if (Rinv && !SWEEP && wave == NW - 1) {   // D^{-T} into Rinv
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (k0 + tr < n && k0 + tg + 4 * v < n) Rinv[k0 + tr + n * (k0 + tg + 4 * v)] = dk[cr + 4 * v];
-        }
         // P(b)^T = D^{-1} A(b, K)^T for b > kb, L^{-1}(K, b) = D^{-1} W(K, b) for b < kb
         for (int q = (SWEEP ? kb : 0) + wave; q < nb - 1; q += NW) {
             const bool below = q >= kb;
@@ -285,18 +281,10 @@ __device__ __forceinline__ void chol_body(const double *__restrict__ G, int n, i
 #pragma unroll
                 for (int v = 0; v < 4; ++v) s_l[k0 + CLD * i0 + cr + 4 * v] = acc[v];
             }
-            // R(K, b) or Rinv(b, K)
-            double *out = below ? Rout : Rinv;
-            if (!out) continue;
-            out += below ? k0 + n * i0 : i0 + n * k0;
-            const int o = below ? tg + n * tr : tr + n * tg, ov = below ? 4 : 4 * n;
-            if (max(k0, i0) + CB <= n) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) out[o + ov * v] = acc[v];
-            } else {
+            if (SWEEP && Rout) {   // R(K, b)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    if (i0 + tr < n && k0 + tg + 4 * v < n) out[o + ov * v] = acc[v];
+                    if (i0 + tr < n && k0 + tg + 4 * v < n) Rout[k0 + tg + 4 * v + n * (i0 + tr)] = acc[v];
             }
         }
         chol_sync();
