@@ -133,7 +133,7 @@ __device__ __forceinline__ void chol_sync() {
 // Where a mode keeps more vectors than the product of the other ranks gives its
 // unfolding signal, the surplus eigenvectors lie in the noise, and which ones come
 // out hangs on the last bits of L^{-1}; ALS sweeps on FP32 data carry such bits on.
-// Both keep the order of operations that their results have had.  Order 80: 22 us
+// Both keep the order of operations that their results have had.  Order 80: 19 us
 // in place of 15.
 template <int NTH, bool SWEEP = false>
 __device__ __forceinline__ void chol_body(const double *__restrict__ G, int n, int64_t ldg,
