@@ -397,9 +397,13 @@ __device__ __forceinline__ void gram_l1_body(const float *__restrict__ Y, int64_
             if (sh > 0) {
 #pragma unroll
                 for (int s = 0; s < LPT; ++s) {
-                    r[s].x = sh == 1 ? r[s].y : (sh == 2 ? r[s].z : r[s].w);
-                    r[s].y = sh == 1 ? r[s].z : r[s].w;
-                    r[s].z = r[s].w;
+                    // values first: a select between the array's elements is one between
+                    // addresses and keeps the whole array in scratch memory (200 x 10485
+                    // in bf16x3 67 us)
+                    const float y = r[s].y, z = r[s].z, w = r[s].w;
+                    r[s].x = sh == 1 ? y : (sh == 2 ? z : w);
+                    r[s].y = sh == 1 ? z : w;
+                    r[s].z = w;
                 }
             }
         }
