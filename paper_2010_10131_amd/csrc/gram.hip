@@ -74,33 +74,37 @@ __global__ __launch_bounds__(SK_T) void gram_skinny_kernel(const float *__restri
 // share the 32 x 32 super tiles of the lower triangle (two of 16 x 16 a side, the
 // upper one of a diagonal super tile left out), MS each at most; where there are
 // fewer than waves, ks groups of waves split a block's rows and are summed at the
-// end.  Two stages of loads are in flight.  Float data is widened as it is stored (widened as it is read, once per
+// end.  Two stages of loads are in flight, of at most TRI_STAGE values each: a
+// stage costs a barrier and a trip through LDS whatever it holds, so short rows
+// take more of them at a time (see tri_sc).  Float data is widened as it is stored (widened as it is read, once per
 // tile and step, 160^4's first mode took 3.2 ms: the conversions and the products
 // share the FP64 units).
 //
-// Bound by the FP64 matrix cores (64 cycles a 16 x 16 x 4 product).  160^4 with
+// Bound by the FP64 matrix cores (64 cycles a 16 x 16 x 4 product) from about 100
+// rows on, by the reading of Y below.  160^4 with
 // 160 of 4.1 M rows: 2.20 ms (1.6 ms of products), 2.45 in the skinny body, whose
 // loading waves widen and sort fragments beside their products.  The later modes,
 // I = 160 with L = 16, 256, ..: 289 us, 967 in 128 x 128 blocks, which pad the
 // triangle of 55 tiles to 160.  64^3 double: 8 us a mode, 20 in one block of 64
 // and few workgroups.
 constexpr int TRI_T = 512, TRI_W = TRI_T / 64;
-constexpr int TRI_SC = 32;
+constexpr int TRI_SC = 32;      // rows of a stage at least
 constexpr int TRI_MAXI = 160;   // 15 super tiles: two per wave
+constexpr int TRI_STAGE = TRI_MAXI * TRI_SC;   // values of a stage at most
 
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 // doubles of a stage (even; reads of the rows beyond I stay within)
-__host__ __device__ inline int tri_stage(int I, bool flat) {
-    return flat ? (I * TRI_SC + 34) / 2 * 2 : 32 * ((I + 31) / 32) * (TRI_SC + 2);
+__host__ __device__ inline int tri_stage(int I, int sc, bool flat) {
+    return flat ? (I * sc + 34) / 2 * 2 : 32 * ((I + 31) / 32) * (sc + 2);
 }
 
-template <typename T, int MS, bool FLAT>
+template <typename T, int MS, int SC, bool FLAT>
 __global__ __launch_bounds__(TRI_T) void gram_tri64_kernel(const T *__restrict__ Y, int64_t L, int I, int64_t P,
                                                           int ks, int nkc, double *__restrict__ partials) {
     constexpr int VE = 16 / sizeof(T);
-    constexpr int NV = (TRI_MAXI * TRI_SC / VE + TRI_T - 1) / TRI_T;   // 16-byte vectors per thread and stage
-    constexpr int SC = TRI_SC, LDP = SC + 2;
+    constexpr int NV = (TRI_STAGE / VE + TRI_T - 1) / TRI_T;   // 16-byte vectors per thread and stage
+    constexpr int LDP = SC + 2;
     typedef T vec_t __attribute__((ext_vector_type(VE)));
     extern __shared__ __align__(16) char s_tri[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -109,7 +113,7 @@ __global__ __launch_bounds__(TRI_T) void gram_tri64_kernel(const T *__restrict__
     const int gw = TRI_W / ks, wg = wave % gw, gk = wave / gw;   // wave of its group, group
     // element (row i, k of the stage) at i * rs + k * cs
     const int rs = FLAT ? 1 : LDP, cs = FLAT ? I : 1;
-    const int stage_e = tri_stage(I, FLAT);
+    const int stage_e = tri_stage(I, SC, FLAT);
     double *s_st = reinterpret_cast<double *>(s_tri);
 
     // super tiles off the diagonal first (four products a step), then those on it
@@ -153,15 +157,17 @@ __global__ __launch_bounds__(TRI_T) void gram_tri64_kernel(const T *__restrict__
     }
     vec_t raws[2][NV];   // two stages in flight
     // the loads alone, unmasked and unconditional (clamped places): a branch or a
-    // select here would wait for them before the stage in hand is multiplied
+    // select here would wait for them before the stage in hand is multiplied.  A
+    // thread's vectors past the stage repeat its last one, or row I - 1 (read on, they
+    // would fetch other workgroups' rows: 10 times the bytes at I = 16).
     const int64_t count = P * I;
     auto load = [&](int st, vec_t (&raw)[NV]) {
-        const int64_t p0 = ((int64_t)st * nkc + kc) * SC;
+        const int64_t p0 = ((int64_t)st * nkc + kc) * SC, last = min(count, (p0 + SC) * I) - VE;
 #pragma unroll
         for (int u = 0; u < NV; ++u) {
             if constexpr (FLAT) {
                 const int64_t e = p0 * I + VE * (tid + TRI_T * u);
-                __builtin_memcpy(&raw[u], Y + min(e, count - VE), 16);
+                __builtin_memcpy(&raw[u], Y + min(e, last), 16);
             } else {
                 const int row = min(row0 + rstep * u, I - 1);
                 __builtin_memcpy(&raw[u], Y + L * row + (p0 + pv < P ? pa + L * I * pb : 0), 16);
@@ -559,17 +565,27 @@ hipError_t launch_ttt_narrow(const T *A, const T *B, int64_t IA, int64_t IB, int
     return hipGetLastError();
 }
 
-// Geometry of the triangle kernel: rows per stage (two stages within the LDS and
-// a thread's vectors), wave groups along the contraction (the fewest products per
-// wave, then the fewest groups), workgroups: one per CU with at least two stages
-// each.
+// Geometry of the triangle kernel: rows per stage, wave groups along the
+// contraction (the fewest products per wave, then the fewest groups), workgroups:
+// one per CU with at least two stages each.
 struct TriShape {
-    int ks, ms, nkc;   // wave groups, super tiles per wave, workgroups
+    int ks, ms, sc, nkc;   // wave groups, super tiles per wave, rows per stage, workgroups
     size_t lds;
 };
 
-int tri_nkc(int64_t P) {
-    return (int)std::max<int64_t>(1, std::min<int64_t>(device_cu_count(), P / (2 * TRI_SC)));
+int tri_nkc(int64_t P, int sc) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(device_cu_count(), P / (2 * sc)));
+}
+
+// Rows per stage: as many as fill its TRI_STAGE values where every CU still gets two
+// stages (32 otherwise, which spreads few rows over more CUs).  512 MB of FP64
+// data, L = 1: I = 16 158 us (256 rows a stage; 554 with 32 and the loads past the
+// stage, 291 in the block kernel), I = 32 111 us (368, 164), I = 64 171 us (210,
+// 190); I = 32, L = 16, 64 MB: 23 us (33, 26).
+int tri_sc(int64_t I, int64_t P) {
+    for (int sc = 8 * TRI_SC; sc > TRI_SC; sc /= 2)
+        if (I * sc <= TRI_STAGE && P >= 2 * (int64_t)sc * device_cu_count()) return sc;
+    return TRI_SC;
 }
 
 TriShape tri_shape(int64_t I, int64_t P, bool flat) {
@@ -584,15 +600,16 @@ TriShape tri_shape(int64_t I, int64_t P, bool flat) {
             t.ms = per;
         }
     }
-    t.lds = std::max((size_t)2 * tri_stage((int)I, flat) * sizeof(double),
+    t.sc = tri_sc(I, P);   // above 32 only for I <= 80: one super tile per wave
+    t.lds = std::max((size_t)2 * tri_stage((int)I, t.sc, flat) * sizeof(double),
                      (size_t)(t.ks - 1) * (TRI_W / t.ks) * t.ms * 4 * 64 * sizeof(f64x4));
-    t.nkc = tri_nkc(P);
+    t.nkc = tri_nkc(P, t.sc);
     return t;
 }
 
-template <typename T, int MS>
+template <typename T, int MS, int SC>
 hipError_t launch_tri_m(const T *A, int64_t L, int64_t I, int64_t P, const TriShape &t, double *partials, hipStream_t s) {
-    auto kern = L == 1 ? gram_tri64_kernel<T, MS, true> : gram_tri64_kernel<T, MS, false>;
+    auto kern = L == 1 ? gram_tri64_kernel<T, MS, SC, true> : gram_tri64_kernel<T, MS, SC, false>;
     if (t.lds > 64 * 1024)
         if (hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)t.lds)) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)t.nkc), dim3(TRI_T), t.lds, s, A, L, (int)I, P, t.ks, t.nkc, partials);
@@ -602,8 +619,16 @@ hipError_t launch_tri_m(const T *A, int64_t L, int64_t I, int64_t P, const TriSh
 template <typename T>
 hipError_t launch_tri(const T *A, int64_t L, int64_t I, int64_t M, double *partials, double *S, hipStream_t s) {
     const TriShape t = tri_shape(I, L * M, L == 1);
-    hipError_t e = t.ms == 1 ? launch_tri_m<T, 1>(A, L, I, L * M, t, partials, s)
-                             : launch_tri_m<T, 2>(A, L, I, L * M, t, partials, s);
+    const int64_t P = L * M;
+    hipError_t e;
+    switch (t.sc) {
+        case 8 * TRI_SC: e = launch_tri_m<T, 1, 8 * TRI_SC>(A, L, I, P, t, partials, s); break;
+        case 4 * TRI_SC: e = launch_tri_m<T, 1, 4 * TRI_SC>(A, L, I, P, t, partials, s); break;
+        case 2 * TRI_SC: e = launch_tri_m<T, 1, 2 * TRI_SC>(A, L, I, P, t, partials, s); break;
+        default:
+            e = t.ms == 1 ? launch_tri_m<T, 1, TRI_SC>(A, L, I, P, t, partials, s)
+                          : launch_tri_m<T, 2, TRI_SC>(A, L, I, P, t, partials, s);
+    }
     if (e != hipSuccess) return e;
     const int ns = sk_ns(I);
     hipLaunchKernelGGL((gram_reduce_kernel<32, true>), dim3(16, ns * (ns + 1) / 2), dim3(256), 0, s, partials, t.nkc, ns,
@@ -703,7 +728,7 @@ size_t gram_ws_bytes(int64_t IA, int64_t IB, int64_t P, bool sym) {
     if (sym && IA <= SK_MAXI) {
         // the skinny path (L = 1) and the triangle kernel (FP64 products)
         const int NS = sk_ns(IA);
-        int nkc = IA <= TRI_MAXI ? tri_nkc(P) : 1;
+        int nkc = IA <= TRI_MAXI ? tri_nkc(P, TRI_SC) : 1;
         for (int prec = P_FP32; prec <= P_BF16X6; ++prec) nkc = std::max(nkc, sk_shape(prec, IA, P).nkc);
         b = std::max(b, (size_t)nkc * (NS * (NS + 1) / 2) * 1024 * sizeof(double));
     }

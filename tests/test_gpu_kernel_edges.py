@@ -202,3 +202,44 @@ def test_gram_edges(api, dims, n, prec):
          "bf16x3": 256 * 2.0 ** -24 + 4 * 2.0 ** -16}[prec]
     assert np.all(np.abs(S - M @ M.T) <= c * (np.abs(M) @ np.abs(M).T))
     np.testing.assert_array_equal(S, S.T)
+
+
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+@pytest.mark.parametrize("dims,n", [((1, 131073), 0), ((5, 140003), 0), ((20, 131072), 0), ((21, 140001), 0), ((40, 65537), 0),
+                                    ((41, 33001), 0), ((80, 32769), 0), ((81, 33000), 0), ((4, 20, 32770), 1),
+                                    ((36, 1, 3650), 1), ((28, 40, 2345), 1), ((8, 33, 8193), 1), ((12, 80, 2731), 1)])
+def test_gram_of_short_rows(api, dims, n, dtype):
+    """FP64 products of few rows over many columns: stages of 32 to 256 columns,
+    rows that end within a stage, contiguous and strided.  K eps of the sums of
+    magnitudes."""
+    rng = np.random.default_rng(sum(dims))
+    X = np.asfortranarray(rng.standard_normal(dims).astype(dtype))
+    S = api.to_numpy(api.gram_mode_n(api.to_device(X), n, "fp64"))
+    M = np.moveaxis(X.astype(np.float64), n, 0).reshape(dims[n], -1)
+    assert np.all(np.abs(S - M @ M.T) <= 4 * M.shape[1] * 2.2e-16 * (np.abs(M) @ np.abs(M).T))
+    np.testing.assert_array_equal(S, S.T)
+
+
+def best_ms(call, reps=8):
+    """Best of several passes after one to warm up, by events on the stream."""
+    import torch
+    call()
+    times = []
+    for _ in range(reps):
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record()
+        call()
+        e[1].record()
+        torch.cuda.synchronize()
+        times.append(e[0].elapsed_time(e[1]))
+    return min(times)
+
+
+@pytest.mark.parametrize("I", [16, 24, 32])
+def test_gram_of_short_rows_is_bound_by_its_reads(api, I):
+    """An FP64 Gram of few rows has little to multiply: over 512 MB it takes no
+    more than three times a plain read of the same data (a sum of squares)."""
+    import torch
+    X = torch.randn((2 ** 26 // I, I), dtype=torch.float64, device="cuda").t()
+    gram, read = best_ms(lambda: api.gram_mode_n(X, 0, "fp64")), best_ms(lambda: api.sumsq(X))
+    assert gram <= 3 * read, (gram, read)
