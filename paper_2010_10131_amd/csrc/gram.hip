@@ -30,13 +30,13 @@
 
 namespace sth {
 
-template <typename T, int PREC, int WT, bool SYM>
+template <typename T, int PREC, int WT, bool SYM, bool FIBRES>
 __global__ __launch_bounds__(256) void gram_kernel(const T *__restrict__ A, const T *__restrict__ B,
                                                    int64_t L, int64_t IA, int64_t IB, int64_t P,
                                                    int64_t kper, int nkc, int nbi, int nbj,
                                                    int nblocks, int64_t total_wg,
                                                    double *__restrict__ partials) {
-    gram_body<T, PREC, WT, SYM>(A, B, L, IA, IB, P, kper, nkc, nbi, nbj, nblocks, total_wg,
+    gram_body<T, PREC, WT, SYM, FIBRES>(A, B, L, IA, IB, P, kper, nkc, nbi, nbj, nblocks, total_wg,
                                 xcd_logical_id(total_wg), partials);
 }
 
@@ -670,7 +670,15 @@ hipError_t launch_gram_t(const T *A, const T *B, int64_t L, int64_t IA, int64_t 
         }
     }
     const size_t lds = (size_t)2 * Frag<PREC>::NQ * TB * 4 * 16;
-    auto kern = gram_kernel<T, PREC, WT, SYM>;
+    auto kern = gram_kernel<T, PREC, WT, SYM, false>;
+    // Long fibres that are not whole octets: two chunks in three or more lie within
+    // one and are read as widely as whole ones.  A kernel of its own: the condition,
+    // in the kernel of the other L, cost those 4 to 9 percent.  300 rows in bf16x3:
+    // L = 1001 194 -> 127 us, 201 133 -> 102, 100 149 -> 117; 64 rows, L = 66 24 ->
+    // 26.  FP64 data in blocks of up to 64 gains nothing (64 rows, L = 1001: 34 -> 38).
+    if constexpr (sizeof(T) == 4 || WT == 4) {
+        if (L % 8 != 0 && L >= 3 * KC) kern = gram_kernel<T, PREC, WT, SYM, true>;
+    }
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;

@@ -16,8 +16,9 @@ struct GramPos {
 // Loads the 8 consecutive rows p0..p0+7 of column i (clamped) of a (L, I, M)
 // tensor, pos the place of p0; rows from pend on repeat an earlier one.  The
 // values are masked when they are stored (gram_mask): a select or a branch here
-// would wait for its loads before the chunk in hand is multiplied.  VEC: L a
-// multiple of 8, so that an octet (p0 a multiple of 8) is one contiguous run.
+// would wait for its loads before the chunk in hand is multiplied.  VEC: the
+// octet is one contiguous run (L a multiple of 8, as p0 is, or a chunk within a
+// fibre) or lies wholly past pend.
 template <typename T, bool VEC>
 __device__ __forceinline__ void gram_load_octet(const T *__restrict__ X, int64_t L, int64_t I,
                                                 int64_t i, GramPos pos, int64_t p0, int64_t pend, T (&x)[8]) {
@@ -70,7 +71,10 @@ __device__ __forceinline__ int64_t xcd_logical_id(int64_t total_wg) {
 // unmasked and their place in the tensor is carried along (no division per
 // chunk).  512^3's later modes in bf16x6: 96 us each (108 with a branch and a
 // division at each octet's load, which waited for the loads at once).
-template <typename T, int PREC, int WT, bool SYM>
+//
+// FIBRES (L no multiple of 8): the octets of a chunk that lies within one fibre
+// are loaded whole, the others value by value.
+template <typename T, int PREC, int WT, bool SYM, bool FIBRES = false>
 __device__ __forceinline__ void gram_body(const T *__restrict__ A, const T *__restrict__ B,
                                           int64_t L, int64_t IA, int64_t IB, int64_t P,
                                           int64_t kper, int nkc, int nbi, int nbj, int nblocks,
@@ -133,18 +137,34 @@ __device__ __forceinline__ void gram_body(const T *__restrict__ A, const T *__re
         pos[s].b = p / L;
         pos[s].a = p - pos[s].b * L;
     }
-    auto load_slab = [&](int64_t pc, auto vec) {
+    auto step = [&](GramPos &p) {   // a chunk further
+        p.a += r32;
+        p.b += q32;
+        if (p.a >= L) {
+            p.a -= L;
+            ++p.b;
+        }
+    };
+    int64_t ca = FIBRES ? pbeg - pbeg / L * L : 0;   // the chunk's place in its fibre
+    auto load_octets = [&](int64_t pc, auto vec) {
         constexpr bool VEC = decltype(vec)::value;
 #pragma unroll
         for (int s = 0; s < UPT; ++s) {
             gram_load_octet<T, VEC>(A, L, IA, i0 + il[s], pos[s], pc + 8 * oct[s], pend, ra[s]);
             if (!diag) gram_load_octet<T, VEC>(B, L, IB, j0 + il[s], pos[s], pc + 8 * oct[s], pend, rb[s]);
-            pos[s].a += r32;
-            pos[s].b += q32;
-            if (pos[s].a >= L) {
-                pos[s].a -= L;
-                ++pos[s].b;
-            }
+            if constexpr (!FIBRES) step(pos[s]);
+        }
+    };
+    auto load_slab = [&](int64_t pc, auto vec) {
+        if constexpr (FIBRES) {
+            if (ca + KC <= L && pc + KC <= pend) load_octets(pc, std::true_type());   // the same for the whole workgroup
+            else load_octets(pc, std::false_type());
+            ca += r32;
+            if (ca >= L) ca -= L;
+#pragma unroll
+            for (int s = 0; s < UPT; ++s) step(pos[s]);
+        } else {
+            load_octets(pc, vec);
         }
     };
     auto store_slab = [&](int64_t pc) {
@@ -213,7 +233,7 @@ __device__ __forceinline__ void gram_body(const T *__restrict__ A, const T *__re
         }
     }
     };
-    if (L % 8 == 0) run(std::true_type());
+    if (!FIBRES && L % 8 == 0) run(std::true_type());
     else run(std::false_type());
     if (!active) return;
     // partial block (TB x TB, column-major) for (kc, q)

@@ -243,3 +243,34 @@ def test_gram_of_short_rows_is_bound_by_its_reads(api, I):
     X = torch.randn((2 ** 26 // I, I), dtype=torch.float64, device="cuda").t()
     gram, read = best_ms(lambda: api.gram_mode_n(X, 0, "fp64")), best_ms(lambda: api.sumsq(X))
     assert gram <= 3 * read, (gram, read)
+
+
+@pytest.mark.parametrize("prec", ["f64", "fp64", "fp32", "bf16x3", "bf16x6"])
+@pytest.mark.parametrize("dims", [(95, 70, 5), (97, 20, 7), (100, 130, 9), (129, 65, 8), (201, 66, 1), (1001, 129, 2), (31, 161, 33)])
+def test_gram_and_ttt_across_fibres(api, dims, prec):
+    """Strided rows whose fibres are not whole octets: chunks within a fibre, across
+    two and across several, and a last one that is not full.  Tolerances as in
+    test_gram_edges."""
+    rng = np.random.default_rng(sum(dims))
+    dtype = np.float64 if prec == "f64" else np.float32
+    X = np.asfortranarray(rng.standard_normal(dims).astype(dtype))
+    Z = np.asfortranarray(rng.standard_normal((dims[0], 17, dims[2])).astype(dtype))
+    p = "fp64" if prec == "f64" else prec
+    M, N = (np.moveaxis(a.astype(np.float64), 1, 0).reshape(a.shape[1], -1) for a in (X, Z))
+    c = {"f64": 4 * M.shape[1] * 2.2e-16, "fp64": 4 * M.shape[1] * 2.2e-16, "fp32": 256 * 2.0 ** -24, "bf16x6": 256 * 2.0 ** -24,
+         "bf16x3": 256 * 2.0 ** -24 + 4 * 2.0 ** -16}[p if p != "f64" else "fp64"]
+    S = api.to_numpy(api.gram_mode_n(api.to_device(X), 1, p))
+    assert np.all(np.abs(S - M @ M.T) <= c * (np.abs(M) @ np.abs(M).T))
+    P = api.to_numpy(api.ttt_mode_n(api.to_device(X), api.to_device(Z), 1, p))
+    assert np.all(np.abs(P - M @ N.T) <= c * (np.abs(M) @ np.abs(N).T))
+
+
+def test_gram_of_odd_fibres_keeps_up_with_whole_ones(api):
+    """Long fibres that are not whole octets cost little more than whole ones: at
+    most one and a half times (within a fibre every load is as wide)."""
+    import torch
+    def gram(L):
+        X = torch.randn((60, 300, L), dtype=torch.float32, device="cuda").permute(2, 1, 0)
+        return best_ms(lambda: api.gram_mode_n(X, 1, "bf16x3"))
+    odd, whole = gram(1001), gram(1000)
+    assert odd <= 1.5 * whole, (odd, whole)
