@@ -397,17 +397,46 @@ hipError_t launch_stream_w(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t
     return hipGetLastError();
 }
 
-// The streaming kernel.  Where its row blocks give every CU eight waves, all
-// RTB r-tiles of a block stay together and Y is read once; with fewer blocks the
-// r-tiles are spread over workgroups of fewer waves (Y, then a few tens of MB at
-// most, is read again from the caches): 512^3 modes 2 and 3 (512 and 64 blocks)
-// took 59 us together in workgroups of eight waves and four r-tiles.
+// Waves per workgroup of the streaming kernel, 0 where the general kernel (half the
+// rows per wave, two workgroups per CU) takes over.  w8 are the workgroups of eight
+// waves and all RTB r-tiles, which read Y once:
+//   * from half a workgroup per CU on they are the fastest form up to one per CU
+//     (512 x 64 in bf16x3, 131 K rows on 255 workgroups: 59 us, 65 in the general
+//     kernel, 113 with the r-tiles dealt two by two to four waves, which reads Y
+//     twice);
+//   * beyond, while the last round of workgroups is full enough: 2200 blocks of 64
+//     rows (275 workgroups) in FP32 148 us, general kernel 131; 5000 blocks 221
+//     and 221, in bf16x3 154 and 160.  One r-tile gains everywhere;
+//   * below, fewer waves and r-tiles spread the rows over the CUs (512 x 16 in
+//     FP32, 16 K rows: 39 us in the general kernel, 17).  With several r-tiles that
+//     reads Y again for each part, which pays where the products are slow (FP32,
+//     512 x 64, 64 K rows: 49.5 us, general 52.4) or Y small; else not (bf16x3,
+//     520 blocks of 64 rows: 34 us, 25).
+// FP64 products of FP32 data: only where full (300 x 20, 19 K rows: 30 us in four
+// waves, 17 in the general kernel) or over few chunks of one r-tile (128 x 16, 16 K
+// rows: 8.7 and 9.2 us; 512 x 8, 13 K rows: 35 and 28).
 template <typename T, int PREC, int RTB>
-hipError_t launch_stream(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K, int64_t Rout, int64_t M,
+int stream_waves(int64_t P, int64_t Rout, int nchunks) {
+    constexpr bool WIDEN = PREC == P_FP64 && sizeof(T) == 4;
+    constexpr int64_t ROWS = 16 * (16 / sizeof(T));
+    const int64_t cu = device_cu_count(), nblocks = (P + ROWS - 1) / ROWS;
+    const int64_t nrb = ((Rout + 15) / 16 + RTB - 1) / RTB, w8 = (nblocks + 7) / 8 * nrb;
+    if (2 * w8 > cu) {
+        if (w8 <= cu) return WIDEN && RTB == 2 ? 0 : 8;
+        const bool full = 20 * w8 >= 17 * cu * ((w8 + cu - 1) / cu);
+        return full || (RTB == 1 && !WIDEN) ? 8 : 0;
+    }
+    const int narrow = nblocks >= cu ? 4 : 2;
+    if (WIDEN) return RTB == 1 && nchunks <= 4 ? narrow : 0;
+    if (RTB == 1 || PREC == P_FP32) return narrow;
+    return nblocks < cu || (RTB == 4 && nblocks * nrb <= 2 * cu) ? narrow : 0;
+}
+
+template <typename T, int PREC, int RTB>
+hipError_t launch_stream(int waves, const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K, int64_t Rout, int64_t M,
                          hipStream_t s) {
-    const int64_t nblocks = (L * M + 16 * (16 / sizeof(T)) - 1) / (16 * (16 / sizeof(T))), cu = device_cu_count();
-    if (nblocks >= 8 * cu) return launch_stream_w<T, PREC, RTB, 8>(Y, Uq, Z, L, K, Rout, M, s);
-    if (nblocks >= cu) return launch_stream_w<T, PREC, (RTB < 2 ? RTB : 2), 4>(Y, Uq, Z, L, K, Rout, M, s);
+    if (waves == 8) return launch_stream_w<T, PREC, RTB, 8>(Y, Uq, Z, L, K, Rout, M, s);
+    if (waves == 4) return launch_stream_w<T, PREC, (RTB < 2 ? RTB : 2), 4>(Y, Uq, Z, L, K, Rout, M, s);
     return launch_stream_w<T, PREC, 1, 2>(Y, Uq, Z, L, K, Rout, M, s);
 }
 
@@ -448,7 +477,8 @@ hipError_t launch_ttm_r(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K,
             return launch_expand<T, PREC, false>(Y, Uq, Z, L, K, Rout, M, nullptr, nullptr, nullptr, s);
         // FP64 accumulators of four tiles x four rows do not fit the registers
         if constexpr (!(PREC == P_FP64 && sizeof(T) == 4 && RTB == 4)) {
-            if (lds <= TTM_LDS_MAX) return launch_stream<T, PREC, RTB>(Y, Uq, Z, L, K, Rout, M, s);
+            const int waves = lds <= TTM_LDS_MAX ? stream_waves<T, PREC, RTB>(L * M, Rout, nchunks) : 0;
+            if (waves) return launch_stream<T, PREC, RTB>(waves, Y, Uq, Z, L, K, Rout, M, s);
         }
     }
     // row tiles per wave: keeps a lane under 256 VGPRs (8 waves per workgroup)

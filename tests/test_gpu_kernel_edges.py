@@ -220,29 +220,32 @@ def test_gram_of_short_rows(api, dims, n, dtype):
     np.testing.assert_array_equal(S, S.T)
 
 
-def best_ms(call, reps=8):
-    """Best of several passes after one to warm up, by events on the stream."""
+def best_ms(call, reps=6, calls=10):
+    """Time of a call: best of several runs of calls one after the other, by events
+    on the stream, after one to warm up."""
     import torch
     call()
     times = []
     for _ in range(reps):
         e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
         e[0].record()
-        call()
+        for _ in range(calls):
+            call()
         e[1].record()
         torch.cuda.synchronize()
-        times.append(e[0].elapsed_time(e[1]))
+        times.append(e[0].elapsed_time(e[1]) / calls)
     return min(times)
 
 
 @pytest.mark.parametrize("I", [16, 24, 32])
 def test_gram_of_short_rows_is_bound_by_its_reads(api, I):
     """An FP64 Gram of few rows has little to multiply: over 512 MB it takes no
-    more than three times a plain read of the same data (a sum of squares)."""
+    more than one and a half times a copy of the same data."""
     import torch
     X = torch.randn((2 ** 26 // I, I), dtype=torch.float64, device="cuda").t()
-    gram, read = best_ms(lambda: api.gram_mode_n(X, 0, "fp64")), best_ms(lambda: api.sumsq(X))
-    assert gram <= 3 * read, (gram, read)
+    to = torch.empty_like(X)
+    gram, copy = best_ms(lambda: api.gram_mode_n(X, 0, "fp64")), best_ms(lambda: to.copy_(X))
+    assert gram <= 1.5 * copy, (gram, copy)
 
 
 @pytest.mark.parametrize("prec", ["f64", "fp64", "fp32", "bf16x3", "bf16x6"])
@@ -274,3 +277,42 @@ def test_gram_of_odd_fibres_keeps_up_with_whole_ones(api):
         return best_ms(lambda: api.gram_mode_n(X, 1, "bf16x3"))
     odd, whole = gram(1001), gram(1000)
     assert odd <= 1.5 * whole, (odd, whole)
+
+
+def strided_ttm(api, dims, R, prec, seed):
+    """One TTM along mode 1 against numpy: FP32 sums of K products (FP64 ones: K
+    eps), rounded to the data type."""
+    rng = np.random.default_rng(seed)
+    dtype = np.float64 if prec == "f64" else np.float32
+    K = dims[1]
+    Y = np.asfortranarray(rng.standard_normal(dims).astype(dtype))
+    U = np.asfortranarray(rng.standard_normal((K, R)))
+    Z = api.to_numpy(api.ttm_mode_n(api.to_device(Y), api.to_device(U), 1, "fp64" if prec == "f64" else prec))
+    Yf = Y.transpose(1, 0, 2).reshape(K, -1).astype(np.float64)
+    ref, bound = U.T @ Yf, np.abs(U).T @ np.abs(Yf)
+    unit = {"f64": 4 * K * 2.2e-16, "fp64": 2.0 ** -23, "fp32": (K + 2) * 2.0 ** -23,
+            "bf16x3": (K + 2) * 2.0 ** -23 + 2.0 ** -15, "bf16x6": (K + 6) * 2.0 ** -23}[prec]
+    assert np.all(np.abs(Z.transpose(1, 0, 2).reshape(R, -1) - ref) <= unit * bound + 1e-30)
+
+
+@pytest.mark.parametrize("prec", ["f64", "fp64", "fp32", "bf16x3", "bf16x6"])
+@pytest.mark.parametrize("dims,R", [((44, 70, 7001), 64), ((44, 70, 7001), 10), ((1004, 66, 303), 33), ((262148, 97, 1), 17),
+                                    ((44, 129, 2501), 60), ((36, 100, 1001), 40), ((36, 100, 1001), 7), ((36, 100, 1001), 100),
+                                    ((20, 130, 121), 64), ((8, 200, 1251), 20), ((28, 80, 6001), 130)])
+def test_strided_ttm_over_many_rows(api, dims, R, prec):
+    """The streaming kernel where a wave goes from one block of rows to the next
+    (the place in the tensor is carried along and wraps within the fibre), with a
+    last block that is not full, and its forms of two, four and eight waves, beside
+    the row counts where the general kernel takes over."""
+    strided_ttm(api, dims, R, prec, sum(dims) + R)
+
+
+def test_strided_ttm_reads_its_input_once(api):
+    """512 x 64 over 131 K rows, one workgroup of eight waves short of filling the
+    chip: at most four fifths of a copy of the 267 MB."""
+    import torch
+    Y = torch.randn((8160, 512, 16), dtype=torch.float32, device="cuda").permute(2, 1, 0)
+    U = api.ttm_factor_prepare(torch.randn((64, 512), dtype=torch.float64, device="cuda").t(), "bf16x3")
+    to = torch.empty_like(Y)
+    ttm, copy = best_ms(lambda: api.ttm_mode_n_prepared(Y, U, 1, 64, "bf16x3")), best_ms(lambda: to.copy_(Y))
+    assert ttm <= 0.8 * copy, (ttm, copy)
