@@ -265,6 +265,7 @@ namespace {
 
 constexpr int TTM_WAVES = 8;
 constexpr size_t TTM_LDS_MAX = 144 * 1024;
+constexpr int64_t TTM_ERR_WGS = 1024;   // fused error sums: workgroups per r-block at most (few partial sums)
 
 template <typename T, int PREC, int NT, int RTB, bool CONTIG, bool ULDS>
 hipError_t launch_ttm_t(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K, int64_t Rout,
@@ -336,42 +337,60 @@ struct VecGrid {
 template <typename T, int PREC>
 constexpr int expand_chunks() { return PREC == P_FP64 && sizeof(T) == 4 ? 1 : 2; }
 
+// Where the expansion kernel serves: contractions of its chunks, but for FP64 data
+// in two chunks between one and eight waves per CU, where the streaming kernel
+// spreads the r-tiles better (50 -> 200 over 30400 rows: 37 us, 30), and the
+// general kernel's error sums the rows (100^3 from 50^3: 47 us, 42).
+template <typename T, int PREC>
+bool use_expand(int64_t P, int nchunks) {
+    if (nchunks > expand_chunks<T, PREC>()) return false;
+    const int64_t cu = device_cu_count(), nblocks = (P + 31) / 32;   // FP64 data: blocks of 32 rows
+    return !(sizeof(T) == 8 && nchunks == 2 && nblocks > cu && nblocks < 8 * cu);
+}
+
 // The expansion kernel (K <= 64): every r-tile from one read of Y where their
-// factor quads fit the LDS, equal ranges of r-tiles otherwise.
+// factor quads fit the LDS, equal ranges of r-tiles otherwise.  ERR: part takes one
+// pair of sums per workgroup; *nparts, its length, is set to their number.
 template <typename T, int PREC, bool ERR>
 hipError_t launch_expand(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K, int64_t Rout, int64_t M,
                          const T *X, double *part, int64_t *nparts, hipStream_t s) {
     constexpr int NQ = Frag<PREC>::NQ;
-    const int64_t P = L * M;
+    const int64_t P = L * M, cu = device_cu_count();
     const int nchunks = (int)((K + KC - 1) / KC), ntiles = (int)((Rout + 15) / 16);
-    // few row blocks: two waves a workgroup and ranges of r-tiles of at most 32
-    // KB, so that every CU has several workgroups (512^3 from 64^3, second
-    // expansion, 512 blocks: 31 -> 22 us)
-    const bool few = !ERR && P < (int64_t)16 * (16 / sizeof(T)) * TTM_WAVES * device_cu_count();
+    // Few row blocks (less than eight waves per CU): two waves a workgroup, ranges
+    // of r-tiles of at most 32 KB, so that every CU has several workgroups, and
+    // enough ranges for eight waves per CU (Y, at most some tens of MB, is read
+    // again from the caches).  50 -> 200 over 5000 rows in FP32: 14.4 us with as
+    // many tiles in a range as fit, 7.0 so (the general kernel 11.3); 20 -> 336 over
+    // 30400: 21.8, 17.1 (19.8).
+    const int64_t nblocks = (P + 16 * (16 / sizeof(T)) - 1) / (16 * (16 / sizeof(T)));
+    const bool few = nblocks < 8 * cu;
     const int fit = (int)((few ? 32 * 1024 : TTM_LDS_MAX) / ((size_t)nchunks * NQ * 1024));
-    const int nrb = (ntiles + fit - 1) / fit, rtn = (ntiles + nrb - 1) / nrb;
+    const int64_t waves = few ? 2 : TTM_WAVES, max_wgs = ERR ? std::min<int64_t>(4 * cu, TTM_ERR_WGS) : 4 * cu;
+    int64_t ranges = few ? std::min<int64_t>(ntiles, 8 * cu / nblocks) : 1;
+    if (ERR) ranges = std::max<int64_t>(1, std::min<int64_t>(ranges, *nparts / std::min((nblocks + 1) / 2, max_wgs)));
+    int rtn = (int)std::min<int64_t>((ntiles + ranges - 1) / ranges, fit);
+    int64_t nrb = (ntiles + rtn - 1) / rtn;
+    rtn = (int)((ntiles + nrb - 1) / nrb);
     const size_t lds = (size_t)nchunks * rtn * NQ * 1024;
     const int64_t per_cu = lds <= 72 * 1024 ? 2 : 1;
-    const int waves = few ? 2 : TTM_WAVES;
-    const VecGrid<T> vg(L, P, waves, (int64_t)device_cu_count() * (few ? 4 : per_cu));
+    const VecGrid<T> vg(L, P, (int)waves, few ? max_wgs : cu * per_cu);
+    if (ERR) *nparts = vg.wgs * nrb;
     const dim3 grid((unsigned)vg.wgs, (unsigned)nrb);
     auto go = [&](auto kern) -> hipError_t {
         if (lds > 64 * 1024) {
             hipError_t r = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (r != hipSuccess) return r;
         }
-        hipLaunchKernelGGL(kern, grid, dim3(64 * waves), lds, s, Y, Uq, Z, L, K, Rout, P, nchunks, ntiles, rtn,
+        hipLaunchKernelGGL(kern, grid, dim3((unsigned)(64 * waves)), lds, s, Y, Uq, Z, L, K, Rout, P, nchunks, ntiles, rtn,
                            vg.nblocks, vg.sa, vg.sb, X, part);
         return hipGetLastError();
     };
-    if (nparts) *nparts = vg.wgs * nrb;
-    if constexpr (!ERR) {
-        if (few) {
-            if constexpr (expand_chunks<T, PREC>() == 2) {
-                if (nchunks == 2) return go(ttm_expand_kernel<T, PREC, 2, 2, false>);
-            }
-            return go(ttm_expand_kernel<T, PREC, 1, 2, false>);
+    if (few) {
+        if constexpr (expand_chunks<T, PREC>() == 2) {
+            if (nchunks == 2) return go(ttm_expand_kernel<T, PREC, 2, 2, ERR>);
         }
+        return go(ttm_expand_kernel<T, PREC, 1, 2, ERR>);
     }
     if constexpr (expand_chunks<T, PREC>() == 2) {
         if (nchunks == 2) return go(ttm_expand_kernel<T, PREC, 2, TTM_WAVES, ERR>);
@@ -473,7 +492,7 @@ hipError_t launch_ttm_r(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K,
         }
     }
     if (ttm_vec_ok<T>(Y, Z, L)) {
-        if (nchunks <= expand_chunks<T, PREC>())
+        if (use_expand<T, PREC>(L * M, nchunks))
             return launch_expand<T, PREC, false>(Y, Uq, Z, L, K, Rout, M, nullptr, nullptr, nullptr, s);
         // FP64 accumulators of four tiles x four rows do not fit the registers
         if constexpr (!(PREC == P_FP64 && sizeof(T) == 4 && RTB == 4)) {
@@ -501,7 +520,6 @@ hipError_t launch_ttm_p(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K,
 }
 
 // ---- the TTM fused with the reconstruction error ----
-constexpr int64_t TTM_ERR_WGS = 1024;   // workgroups per r-block at most (partial sums stay small)
 
 int ttm_err_rtb(int64_t Rout) {
     const int64_t ntiles = (Rout + 15) / 16;
@@ -548,12 +566,11 @@ hipError_t launch_ttm_err_r(const T *Y, const uint4 *Uq, const T *X, int64_t L, 
 template <typename T, int PREC>
 hipError_t launch_ttm_err_p(const T *Y, const uint4 *Uq, const T *X, int64_t L, int64_t K, int64_t Rout,
                             int64_t M, double *part, double *out, hipStream_t s) {
-    const int64_t nchunks = (K + KC - 1) / KC;
-    // the expansion kernel's workgroups (at most two per CU and r-range) fit the
-    // partial sums' buffer where the factor fits the LDS in one range
-    if (ttm_vec_ok<T>(Y, X, L) && nchunks <= expand_chunks<T, PREC>() &&
+    const int nchunks = (int)((K + KC - 1) / KC);
+    // where the factor fits the LDS in one range
+    if (ttm_vec_ok<T>(Y, X, L) && use_expand<T, PREC>(L * M, nchunks) &&
         (size_t)nchunks * ((Rout + 15) / 16) * Frag<PREC>::NQ * 1024 <= TTM_LDS_MAX) {
-        int64_t np = 0;
+        int64_t np = (int64_t)(ttm_err_part_doubles(Rout) / 2);
         hipError_t e = launch_expand<T, PREC, true>(Y, Uq, nullptr, L, K, Rout, M, X, part, &np, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(sum_pairs_kernel, dim3(1), dim3(256), 0, s, part, np, out);

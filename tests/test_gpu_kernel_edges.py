@@ -316,3 +316,51 @@ def test_strided_ttm_reads_its_input_once(api):
     to = torch.empty_like(Y)
     ttm, copy = best_ms(lambda: api.ttm_mode_n_prepared(Y, U, 1, 64, "bf16x3")), best_ms(lambda: to.copy_(Y))
     assert ttm <= 0.8 * copy, (ttm, copy)
+
+
+@pytest.mark.parametrize("prec", ["f64", "fp64", "fp32", "bf16x3", "bf16x6"])
+@pytest.mark.parametrize("dims,R", [((44, 40, 7001), 100), ((1004, 20, 303), 16), ((262148, 33, 1), 17), ((36, 64, 1001), 200),
+                                    ((4, 50, 16), 700), ((100, 50, 50), 100), ((28, 7, 3001), 70), ((8, 32, 9), 1000)])
+def test_expansion_over_many_rows_and_few(api, dims, R, prec):
+    """The expansion kernel where a wave goes from one block of rows to the next,
+    and where few rows are spread over ranges of r-tiles, down to one tile each."""
+    strided_ttm(api, dims, R, prec, sum(dims) + R)
+
+
+@pytest.mark.parametrize("dims,ranks", [((300, 1004, 37), (3, 4, 20)), ((44, 7001, 80), (4, 3, 40)), ((100, 100, 100), (5, 6, 50)),
+                                        ((200, 152, 336), (4, 5, 40)), ((2, 2, 500), (2, 2, 4)), ((4, 2, 2100), (2, 2, 3))])
+@pytest.mark.parametrize("prec", ["f64", "fp64", "fp32", "bf16x6"])
+def test_error_sums_over_many_rows_and_few(api, dims, ranks, prec):
+    """The fused error sums in the same forms: the partial sums of every workgroup
+    and range are added up, each value once."""
+    import torch
+    dtype = torch.float64 if prec == "f64" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(sum(dims))
+    def column_major(shape, t):
+        return torch.randn(shape[::-1], generator=gen, device="cuda", dtype=t).permute(*range(len(shape) - 1, -1, -1))
+    G, X = column_major(ranks, dtype), column_major(dims, dtype)
+    U = [column_major((d, r), torch.float64) / d ** 0.5 for d, r in zip(dims, ranks)]
+    U = [u.t().contiguous().t() for u in U]
+    out = api.tucker_error(X, G, U, "fp64" if prec == "f64" else prec).cpu().numpy()
+    T = G.double()
+    for n, u in enumerate(U):   # G x_n U_n
+        T = torch.tensordot(u, T, dims=([1], [n])).movedim(0, n)
+    want = [float(((X.double() - T) ** 2).sum()), float((X.double() ** 2).sum())]
+    np.testing.assert_allclose(out, want, rtol=1e-12 if prec == "f64" else 1e-5)
+
+
+def test_small_expansion_spreads_over_the_chip(api):
+    """50 -> 100 over 5000 rows has 80 blocks of rows: in one range of r-tiles most
+    CUs had nothing to do.  Ten times the outputs in at most twice the time."""
+    import torch
+    Y = torch.randn((50, 50, 100), dtype=torch.float32, device="cuda").permute(2, 1, 0)
+    def expand(R):
+        U = api.ttm_factor_prepare(torch.randn((R, 50), dtype=torch.float64, device="cuda").t(), "fp32")
+        Z = api.ttm_mode_n_prepared(Y, U, 1, R, "fp32")
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            for _ in range(20):
+                api.ttm_mode_n_prepared(Y, U, 1, R, "fp32", out=Z)
+        return best_ms(g.replay, calls=2)
+    many, few = expand(320), expand(32)
+    assert many <= 2 * few, (many, few)
