@@ -476,11 +476,22 @@ hipError_t launch_ttm_r(const T *Y, const uint4 *Uq, T *Z, int64_t L, int64_t K,
     }
     if constexpr (PREC == P_FP64) {
         // few rows and a long contraction: the eight waves of a workgroup split
-        // K (at least four chunks each) where the general kernel would leave
-        // CUs without a workgroup
+        // K (at least four chunks each) where the general kernel would leave many
+        // CUs without a workgroup (times against it, by its workgroups):
+        //   contiguous rows: K = 1000, R = 33 188 0.97, 235 1.26; K = 4000 235 0.90;
+        //   strided rows cost the split more (a lane's rows are not whole lines):
+        //   K = 1000, R = 100 142 1.07; K = 8000 188 0.96; one range of several
+        //   r-tiles, K = 2000 157 0.84, 188 1.04; FP64 data, one r-tile, K = 1000
+        //   47 0.80, 94 1.45
         constexpr int NTG = RTB == 1 ? 2 : 1;
-        const int64_t P = L * M, ntiles = (Rout + 15) / 16, nrb = (ntiles + RTB - 1) / RTB;
-        if (nchunks >= 4 * KW_WAVES && (P + 16 * NTG * TTM_WAVES - 1) / (16 * NTG * TTM_WAVES) * nrb < device_cu_count()) {
+        const int64_t P = L * M, ntiles = (Rout + 15) / 16, nrb = (ntiles + RTB - 1) / RTB, cu = device_cu_count();
+        const bool many_chunks = nchunks >= 12 * KW_WAVES;
+        int64_t limit;   // workgroups of the general kernel, below which the split is taken
+        if (contig) limit = many_chunks ? cu : 3 * cu / 4;
+        else if (many_chunks) limit = 3 * cu / 4;
+        else if (RTB > 1 && nrb == 1) limit = 5 * cu / 8;
+        else limit = sizeof(T) == 8 && RTB == 1 && nchunks < 6 * KW_WAVES ? cu / 4 : cu / 2;
+        if (nchunks >= 4 * KW_WAVES && (P + 16 * NTG * TTM_WAVES - 1) / (16 * NTG * TTM_WAVES) * nrb < limit) {
             const dim3 grid((unsigned)((P + 15) / 16), (unsigned)nrb);
             if (contig)
                 hipLaunchKernelGGL((ttm_kw_kernel<T, RTB, true>), grid, dim3(64 * KW_WAVES), 0, s, Y, Uq, Z, L, K,

@@ -364,3 +364,21 @@ def test_small_expansion_spreads_over_the_chip(api):
         return best_ms(g.replay, calls=2)
     many, few = expand(320), expand(32)
     assert many <= 2 * few, (many, few)
+
+
+@pytest.mark.parametrize("K,R,L,M,dtype", [(1000, 5, 30, 1000, "float64"), (1000, 33, 30, 1000, "float64"), (1000, 33, 30, 1000, "float32"),
+                                           (1000, 33, 1, 30000, "float64"), (1000, 33, 1, 30000, "float32")])
+def test_long_contraction_over_many_rows(api, K, R, L, M, dtype):
+    """30000 rows are enough for the general kernel, which has CUs to spare until
+    then: at most 1.75 times the time of half the rows (the waves of a workgroup
+    splitting K are bound by what they read and took twice the time)."""
+    import torch
+    t = getattr(torch, dtype)
+    U = api.ttm_factor_prepare(torch.randn((R, K), dtype=torch.float64, device="cuda").t(), "fp64")
+    def time(m):
+        Y = torch.randn((m, K, L), dtype=t, device="cuda").permute(2, 1, 0)
+        Y, n = (Y, 1) if L > 1 else (Y.reshape(K, m), 0)
+        Z = api.ttm_mode_n_prepared(Y, U, n, R, "fp64")
+        return best_ms(lambda: api.ttm_mode_n_prepared(Y, U, n, R, "fp64", out=Z))
+    whole, half = time(M), time(M // 2)
+    assert whole <= 1.75 * half, (whole, half)
