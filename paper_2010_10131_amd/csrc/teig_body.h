@@ -908,14 +908,18 @@ __device__ void ts_body(const double *__restrict__ S, int64_t lds, int n, int R,
         const int nzw = (R + 63) / 64;   // waves with a vector
         if (wave < nzw) {
             if (tid < R) {
-                // inside a cluster the shift moves off the eigenvalue by a few eps
-                // ||T||: (T - shift)^{-1} then weights the whole eigenspace alike,
-                // and the vectors' random starts keep them apart (at the same
-                // computed eigenvalue they would all turn into one direction, and
-                // Gram-Schmidt would magnify their residuals)
+                // inside a cluster the shift moves off the eigenvalue: (T - shift)^{-1}
+                // then weights the whole eigenspace alike, and the vectors' random
+                // starts keep them apart (at the same computed eigenvalue they would
+                // all turn into one direction, and Gram-Schmidt would magnify their
+                // residuals).  By 32 eps ||T|| where the eigenvalues are equal to
+                // rounding, well beyond their spread (100 eigenvalues, three values: the
+                // residuals reach 2e-13 ||S||, 1e-10 at 4 eps); else by 4, less than the
+                // distances within the cluster
                 const double ulp = 2.220446049250313e-16 * tnorm;
                 double lm = s_lam[tid];
-                if (tid > 0 && s_lam[tid - 1] - lm <= 1e-9 * tnorm) lm += 4.0 * ulp;
+                const double above = tid > 0 ? s_lam[tid - 1] - lm : HUGE_VAL;
+                if (above <= 1e-9 * tnorm) lm += (above <= 8.0 * ulp ? 32.0 : 4.0) * ulp;
                 ts_inverse(s_de, s_e, s_re, n, R, lm, ulp, tid, F, Z, ldz, s_inv);
             }
         } else if (n > 2) {

@@ -382,3 +382,22 @@ def test_long_contraction_over_many_rows(api, K, R, L, M, dtype):
         return best_ms(lambda: api.ttm_mode_n_prepared(Y, U, n, R, "fp64", out=Z))
     whole, half = time(M), time(M // 2)
     assert whole <= 1.75 * half, (whole, half)
+
+
+@pytest.mark.parametrize("levels", [(1.0, 1e-12), (1.0, 1e-4), (1.0, 0.5, 0.25)])
+@pytest.mark.parametrize("n", [16, 33, 64, 100, 128])
+def test_direct_solver_on_large_clusters(api, n, levels):
+    """Two or three eigenvalues that many eigenvectors share: Gram-Schmidt inside a
+    cluster must not magnify what a vector has outside its eigenspace.  The solver's
+    shifts lie within 32 eps ||T|| of the eigenvalues, ||T|| <= 2 ||S||: residuals
+    within 64 n eps ||S||."""
+    for seed in range(3):
+        rng = np.random.default_rng(n + seed)
+        Q = np.linalg.qr(rng.standard_normal((n, n)))[0]
+        Y = np.asfortranarray(Q * np.sqrt(np.array(levels)[(len(levels) * np.arange(n)) // n]))
+        S = Y @ Y.T
+        for R in ((n + 1) // 2, n):
+            _, U, ev, _ = api.mode_step(api.to_device(Y), 0, R, "eig", "fp64", "fp64")
+            U, ev = api.to_numpy(U), ev.cpu().numpy()
+            assert np.linalg.norm(S @ U - U * ev, 2) <= 64 * n * 2.2e-16
+            np.testing.assert_allclose(U.T @ U, np.eye(R), rtol=0, atol=8 * n * 2.2e-16)
