@@ -351,7 +351,7 @@ AlsBufs als_bufs(double *base, int64_t I, int64_t R) {
 // the matrix cores for FP64 data, in LDS panels for FP32 data (see gemm_f64).
 hipError_t als_gemm(int dtype, int ta, int tb, int m, int n, int k, const double *A, int64_t lda, const double *B,
                     int64_t ldb, double *C, int64_t ldc, void *ws, hipStream_t s) {
-    if (dtype != DT_F64) return gemm_f64(ta, tb, m, n, k, 1.0, A, lda, B, ldb, 0.0, C, ldc, ws, s);
+    if (dtype != DT_F64) return gemm_f64(ta, tb, m, n, k, A, lda, B, ldb, C, ldc, ws, s);
     return ta ? gemm_tn(m, n, k, A, lda, B, ldb, C, ldc, ws, s) : gemm_nn(tb != 0, m, n, k, A, lda, B, ldb, C, ldc, s);
 }
 
@@ -1181,7 +1181,6 @@ struct BatchLaunchT {
     int len;
     int64_t total;
     int cls;
-    int l1 = 0;   // every tensor of the list has L = 1
 };
 struct BatchStepT {
     size_t descs_off;
@@ -1365,8 +1364,6 @@ extern "C" sth_status sthosvd_plan_batched_tiles(const sth_desc *descs, int32_t 
                 }
             if (!gl.empty()) {
                 BatchLaunchT G = make(gl, gw, cls);
-                G.l1 = 1;
-                for (int32_t t : gl) G.l1 &= sd[s][t].L == 1 ? 1 : 0;
                 T.gram.push_back(G);
                 T.reduce.push_back(make(gl, gb, cls));
             }
@@ -1447,7 +1444,6 @@ extern "C" sth_status sthosvd_run_batched(const sth_batch_plan *p, const void *c
         b.len = L.len;
         b.total = L.total;
         b.cls = L.cls;
-        b.l1 = L.l1;
         return b;
     };
     for (int s2 = 0; s2 < p->N; ++s2) {

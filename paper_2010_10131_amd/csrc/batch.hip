@@ -71,27 +71,15 @@ __global__ __launch_bounds__(256) void batch_gram_kernel(const BatchStep *__rest
     double *part = (double *)(ws + d.part_off);
     const int64_t local = lid - pref[k];
     const int64_t P = d.L * d.M;
-    if (d.L == 1 && WT >= 2) {
-        // the 16-byte loaders need only 4-byte aligned rows
-        if constexpr (WT == 2) {
-            if (d.I >= 4) {
-                gram_l1_body<PREC, 2, 2, 2, 2, true, false, true>(Y, d.I, P, d.kper, d.nkc, d.nblocks, d.gram_wg, local, part);
-                return;
-            }
-        }
-        if (d.I >= 4)
-            gram_l1_body<PREC, WT, WT, 2, 2, true>(Y, d.I, P, d.kper, d.nkc, d.nblocks, d.gram_wg, local, part);
-        else
-            gram_l1_body<PREC, WT, WT, 2, 2, false>(Y, d.I, P, d.kper, d.nkc, d.nblocks, d.gram_wg, local, part);
-    } else {
+    if constexpr (WT == 2)
+        gram_l1_body<PREC, 2, 2, 2, 2, false, true>(Y, d.I, P, d.kper, d.nkc, d.nblocks, d.gram_wg, local, part);
+    else
         gram_body<float, PREC, WT, true>(Y, Y, d.L, d.I, d.I, P, d.kper, d.nkc, d.nbi, d.nbi,
                                         d.nblocks, d.gram_wg, local, part);
-    }
 }
 
-// The 128-wide class of a launch whose tensors all have L = 1 (the first mode
-// step): eight waves of 64 x 32 tiles, as the single-tensor mode-1 Gram, with
-// the 16-byte loads (any I >= 4).
+// The 128-wide class: eight waves of 64 x 32 tiles, as the single-tensor mode-1
+// Gram, with the 16-byte loads.
 template <int PREC>
 __global__ __launch_bounds__(512) void batch_gram_l1w_kernel(const BatchStep *__restrict__ descs,
                                                             const int32_t *__restrict__ list,
@@ -107,10 +95,7 @@ __global__ __launch_bounds__(512) void batch_gram_l1w_kernel(const BatchStep *__
     double *part = (double *)(ws + d.part_off);
     const int64_t local = lid - pref[k];
     const int64_t P = d.L * d.M;
-    if (d.I >= 4)
-        gram_l1_body<PREC, 4, 2, 2, 4, true, false, true>(Y, d.I, P, d.kper, d.nkc, d.nblocks, d.gram_wg, local, part);
-    else
-        gram_l1_body<PREC, 4, 2, 2, 4, false>(Y, d.I, P, d.kper, d.nkc, d.nblocks, d.gram_wg, local, part);
+    gram_l1_body<PREC, 4, 2, 2, 4, false, true>(Y, d.I, P, d.kper, d.nkc, d.nblocks, d.gram_wg, local, part);
 }
 
 // The skinny class (first mode step, I <= SK_MAXI): each workgroup of a
@@ -645,7 +630,7 @@ hipError_t launch_bgram_p(int wt, const BatchLaunch &bl, const BatchTables &t, c
                            bl.len, bl.total, ws, Xp);
         return hipGetLastError();
     }
-    if (wt == 4 && bl.l1) {
+    if (wt == 4) {
         auto kern = batch_gram_l1w_kernel<PREC>;
         if (lds > 64 * 1024) {
             hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -656,11 +641,7 @@ hipError_t launch_bgram_p(int wt, const BatchLaunch &bl, const BatchTables &t, c
                            bl.len, bl.total, ws, Xp);
         return hipGetLastError();
     }
-    switch (wt) {
-        case 1: return launch_bgram<PREC, 1>(bl, t, ws, Xp, lds, s);
-        case 2: return launch_bgram<PREC, 2>(bl, t, ws, Xp, lds, s);
-        default: return launch_bgram<PREC, 4>(bl, t, ws, Xp, lds, s);
-    }
+    return wt == 1 ? launch_bgram<PREC, 1>(bl, t, ws, Xp, lds, s) : launch_bgram<PREC, 2>(bl, t, ws, Xp, lds, s);
 }
 
 template <int PREC, int RTB>

@@ -57,41 +57,6 @@ __global__ __launch_bounds__(EIG_THREADS) void jacobi_small_kernel(const double 
     jacobi_small_body<VLDS>(S, n, R, Vg, U, lam, tol, max_sweeps, flag);
 }
 
-// Sign rule on the columns of an n x R matrix: the entry of largest
-// magnitude of each column is made positive (first index on ties).
-__global__ void sign_fix_kernel(double *__restrict__ U, int n, int R) {
-    const int r = blockIdx.x;
-    __shared__ double s_v[256];
-    __shared__ int s_i[256];
-    double best = -1.0;
-    int arg = 0;   // in range even when every entry is NaN (no comparison succeeds)
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        double v = fabs(U[i + (int64_t)n * r]);
-        if (v > best) {
-            best = v;
-            arg = i;
-        }
-    }
-    s_v[threadIdx.x] = best;
-    s_i[threadIdx.x] = arg;
-    __syncthreads();
-    for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) {
-            double v2 = s_v[threadIdx.x + o];
-            int i2 = s_i[threadIdx.x + o];
-            if (v2 > s_v[threadIdx.x] || (v2 == s_v[threadIdx.x] && i2 < s_i[threadIdx.x])) {
-                s_v[threadIdx.x] = v2;
-                s_i[threadIdx.x] = i2;
-            }
-        }
-        __syncthreads();
-    }
-    const bool neg = U[s_i[0] + (int64_t)n * r] < 0.0;
-    __syncthreads();
-    if (neg)
-        for (int i = threadIdx.x; i < n; i += blockDim.x) U[i + (int64_t)n * r] = -U[i + (int64_t)n * r];
-}
-
 // SMALL: n <= TE_LDS_N (teig_small); ZLDS: see teig_body
 template <bool SMALL, bool ZLDS>
 __global__ __launch_bounds__(TE_T) void teig_kernel(const double *__restrict__ S, int64_t lds, int n, int R,

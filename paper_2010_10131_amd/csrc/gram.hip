@@ -54,10 +54,10 @@ __global__ __launch_bounds__((gram_l1_eight_waves<PREC, WT>() ? 512 : 256)) void
     const float *__restrict__ Y, int64_t I, int64_t P, int64_t kper, int nkc, int nblocks,
     int64_t total_wg, double *__restrict__ partials) {
     if constexpr (gram_l1_eight_waves<PREC, WT>())
-        gram_l1_body<PREC, 4, 2, 2, 4, true, FULLI>(Y, I, P, kper, nkc, nblocks, total_wg,
+        gram_l1_body<PREC, 4, 2, 2, 4, FULLI>(Y, I, P, kper, nkc, nblocks, total_wg,
                                                     xcd_logical_id(total_wg), partials);
     else
-        gram_l1_body<PREC, WT, WT, 2, 2, true, FULLI>(Y, I, P, kper, nkc, nblocks, total_wg,
+        gram_l1_body<PREC, WT, WT, 2, 2, FULLI>(Y, I, P, kper, nkc, nblocks, total_wg,
                                                       xcd_logical_id(total_wg), partials);
 }
 
@@ -117,12 +117,12 @@ __global__ __launch_bounds__(TRI_T) void gram_tri64_kernel(const T *__restrict__
     double *s_st = reinterpret_cast<double *>(s_tri);
 
     // super tiles off the diagonal first (four products a step), then those on it
-    // (three), dealt to the SIMDs (wave mod 4) in turn; -1: none
+    // (three); -1: none
     int q[MS], oa[MS], ob[MS];
     bool diag[MS];
 #pragma unroll
     for (int m = 0; m < MS; ++m) {
-        const int u = gw >= 4 ? (wg & 3) + 4 * ((wg >> 2) + (gw >> 2) * m) : wg + gw * m;
+        const int u = wg + gw * m;
         int bi = 0, bj = 0;
         diag[m] = u >= noff;
         if (u < noff) {   // (1, 0), (2, 0), (2, 1), ..
@@ -474,7 +474,7 @@ struct SkShape {
 
 SkShape sk_shape(int prec, int64_t I, int64_t P) {
     SkShape k;
-    const int NQ = prec == P_FP64 ? 4 : (prec == P_BF16X6 ? 3 : 2);
+    const int NQ = prec == P_BF16X6 ? 3 : 2;
     const int64_t TBp = 32 * (int64_t)sk_ns(I);
     k.ch = prec == P_BF16X6 ? 4 : 8;   // bf16x6 at 8 chunks would spill registers
     while (k.ch > 1 && (TBp * k.ch > SK_T || 2 * k.ch * NQ * 4 * TBp * 16 > 150 * 1024)) k.ch >>= 1;
@@ -484,7 +484,7 @@ SkShape sk_shape(int prec, int64_t I, int64_t P) {
 }
 
 size_t sk_lds(int prec, int64_t I, int ch) {
-    const int NQ = prec == P_FP64 ? 4 : (prec == P_BF16X6 ? 3 : 2);
+    const int NQ = prec == P_BF16X6 ? 3 : 2;
     return (size_t)2 * ch * NQ * 4 * 32 * sk_ns(I) * 16;
 }
 
@@ -651,7 +651,7 @@ hipError_t launch_gram_t(const T *A, const T *B, int64_t L, int64_t IA, int64_t 
         if constexpr (PREC != P_FP64) {
             if (L == 1 && IA <= SK_MAXI) return launch_skinny<PREC>(A, IA, M, partials, S, s);
         }
-        if (L == 1 && WT >= 2) {
+        if (WT >= 2 && L == 1) {
             hipError_t e = launch_gram_l1<PREC, WT>(A, IA, M, g, partials, s);
             if (e != hipSuccess) return e;
             hipLaunchKernelGGL((gram_reduce_kernel<TB, SYM>), dim3((TB * TB + 63) / 64, g.nblocks),

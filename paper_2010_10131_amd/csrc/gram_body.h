@@ -318,7 +318,7 @@ __device__ __forceinline__ int l1_row(int r) { return r ^ ((r >> 4) & 3); }
 // one operand twice, from cache) and taken as it is: rows from pend on become
 // zero when they are stored.  A branch or a select at the load makes the compiler
 // wait for the chunks in flight before the one in hand is multiplied.
-// VEC4: I >= 4, 16-byte loads of four columns (any alignment).
+// I >= 4: 16-byte loads of four columns (any alignment).
 // FULLI: I is a multiple of TB; see below.
 // V4LD (batched mode-1 launches, any I >= 4): thread (parity, operand, row quad
 // iq, group g) owns rows 4 iq .. 4 iq + 3 of one operand and the 8 columns g of
@@ -329,7 +329,7 @@ __device__ __forceinline__ int l1_row(int r) { return r ^ ((r >> 4) & 3); }
 // single-tensor path keeps those.
 // With the selects at the loads (and, V4LD, 4-way bank conflicts of its stores)
 // the Grams of the later modes of 256 mixed tensors took 2.80 ms, now 2.12 ms.
-template <int PREC, int WTI, int WTJ, int WI, int WJ, bool VEC4, bool FULLI = false, bool V4LD = false>
+template <int PREC, int WTI, int WTJ, int WI, int WJ, bool FULLI = false, bool V4LD = false>
 __device__ __forceinline__ void gram_l1_body(const float *__restrict__ Y, int64_t I, int64_t P,
                                              int64_t kper, int nkc, int nblocks, int64_t total_wg,
                                              int64_t lid, double *__restrict__ partials) {
@@ -390,15 +390,9 @@ __device__ __forceinline__ void gram_l1_body(const float *__restrict__ Y, int64_
         for (int s = 0; s < LPT; ++s) {
             const int64_t p = pc + ph + PH * s;
             const float *src = Y + I * (p < pend ? p : pend - 1);
-            if (VEC4) {   // I >= 4; the quad across column I - 1 is read from I - 4 on
-                const f32x4u v = *reinterpret_cast<const f32x4u *>(src + min(col, I - 4));
-                r[s] = make_float4(v.x, v.y, v.z, v.w);
-            } else {
-                r[s].x = src[min(col, I - 1)];
-                r[s].y = src[min(col + 1, I - 1)];
-                r[s].z = src[min(col + 2, I - 1)];
-                r[s].w = src[min(col + 3, I - 1)];
-            }
+            // the quad across column I - 1 is read from I - 4 on
+            const f32x4u v = *reinterpret_cast<const f32x4u *>(src + min(col, I - 4));
+            r[s] = make_float4(v.x, v.y, v.z, v.w);
         }
     };
     // pc: the chunk's first row; its rows from pend on become zero here
@@ -410,7 +404,7 @@ __device__ __forceinline__ void gram_l1_body(const float *__restrict__ Y, int64_
                 if (p >= pend) (&r[0].x)[s] = 0.f;
             }
         }
-        if constexpr (VEC4 && !FULLI) {
+        if constexpr (!FULLI) {
             // and moved into place here (columns from I on hold anything: they
             // reach no output that is read)
             const int64_t sh = (op ? j0 : i0) + 4 * iq - (I - 4);

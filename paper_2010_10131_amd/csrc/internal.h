@@ -65,12 +65,11 @@ hipError_t gemm_tn(int m, int n, int k, const double *A, int64_t lda, const doub
                    int64_t ldc, void *ws, hipStream_t s);
 hipError_t gemm_nn(bool tb, int m, int n, int k, const double *A, int64_t lda, const double *B, int64_t ldb,
                    double *C, int64_t ldc, hipStream_t s);
-// C = alpha op(A) op(B) + beta C in LDS panels (ws: gemm_ws_bytes)
+// C = op(A) op(B) in LDS panels (ws: gemm_ws_bytes)
 int gemm_splits(int m, int n, int k);
 size_t gemm_ws_bytes(int m, int n, int k);
-hipError_t gemm_f64(int ta, int tb, int m, int n, int k, double alpha, const double *A,
-                    int64_t lda, const double *B, int64_t ldb, double beta, double *C, int64_t ldc,
-                    void *ws, hipStream_t s);
+hipError_t gemm_f64(int ta, int tb, int m, int n, int k, const double *A, int64_t lda, const double *B,
+                    int64_t ldb, double *C, int64_t ldc, void *ws, hipStream_t s);
 hipError_t chol_launch(const double *G, int n, int64_t ldg, double shift_rel, double *R,
                        double *Rinv, int64_t *flag, hipStream_t s);
 hipError_t sumsq_launch(int dtype, const void *x, const void *y, int64_t count, double *out,
@@ -102,7 +101,6 @@ struct BatchLaunch {
     int len;
     int64_t total;
     int cls;  // tile class (Gram: WT, or BATCH_SKINNY; TTM: r-tiles per workgroup)
-    int l1;   // Gram: every tensor of the list has L = 1
 };
 struct BatchTables {
     const BatchStep *descs;  // device

@@ -4,7 +4,7 @@
 //   gemm_tn       C = A^T B over a long contraction, split over workgroups
 //                 with a fixed-order reduction (deterministic)
 //   gemm_nn       C = A op(B) with a short contraction
-//   gemm_f64      C = alpha op(A) op(B) + beta C in LDS panels (FP32 data)
+//   gemm_f64      C = op(A) op(B) in LDS panels (FP32 data)
 //   chol_kernel   one workgroup: G (+ shift) = R^T R (Cholesky, R upper),
 //                 writes R and R^{-1}; used for the normal equations of
 //                 Alg. 3 and for Cholesky-QR
@@ -171,9 +171,9 @@ constexpr int GK = 128;  // k-extent staged in LDS per step
 // once (coalesced along the contiguous index of each operand), then runs
 // GK rank-1 updates from LDS: one global round trip per 128 values of k.
 __global__ __launch_bounds__(256) void gemm_f64_kernel(int ta, int tb, int m, int n, int k,
-                                                       double alpha, const double *__restrict__ A,
+                                                       const double *__restrict__ A,
                                                        int64_t lda, const double *__restrict__ B,
-                                                       int64_t ldb, double beta, double *__restrict__ C,
+                                                       int64_t ldb, double *__restrict__ C,
                                                        int64_t ldc, int kslice, double *__restrict__ part) {
     extern __shared__ __align__(16) double s_gemm[];
     double *sA = s_gemm;                  // sA[kk * (GT + 1) + r] = op(A)(row0 + r, kc + kk)
@@ -228,12 +228,8 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(int ta, int tb, int m, in
         for (int y = 0; y < 2; ++y) {
             int r = row0 + tx + 16 * x, c = col0 + ty + 16 * y;
             if (r < m && c < n) {
-                if (part) {
-                    part[(int64_t)kz * m * n + r + (int64_t)m * c] = acc[x][y];
-                } else {
-                    double old = (beta != 0.0) ? C[r + ldc * c] : 0.0;
-                    C[r + ldc * c] = alpha * acc[x][y] + beta * old;
-                }
+                if (part) part[(int64_t)kz * m * n + r + (int64_t)m * c] = acc[x][y];
+                else C[r + ldc * c] = acc[x][y];
             }
         }
 }
@@ -241,14 +237,13 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(int ta, int tb, int m, in
 constexpr size_t GEMM_LDS = (size_t)2 * GK * (GT + 1) * sizeof(double);
 
 __global__ void gemm_f64_reduce_kernel(int m, int n, int nz, const double *__restrict__ part,
-                                   double alpha, double beta, double *__restrict__ C, int64_t ldc) {
+                                       double *__restrict__ C, int64_t ldc) {
     int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= (int64_t)m * n) return;
     int r = (int)(e % m), c = (int)(e / m);
     double s = 0.0;
     for (int z = 0; z < nz; ++z) s += part[(int64_t)z * m * n + e];
-    double old = (beta != 0.0) ? C[r + ldc * c] : 0.0;
-    C[r + ldc * c] = alpha * s + beta * old;
+    C[r + ldc * c] = s;
 }
 
 size_t gemm_ws_bytes(int m, int n, int k) {
@@ -267,9 +262,8 @@ int gemm_splits(int m, int n, int k) {
     return std::max(nz, 1);
 }
 
-hipError_t gemm_f64(int ta, int tb, int m, int n, int k, double alpha, const double *A,
-                    int64_t lda, const double *B, int64_t ldb, double beta, double *C, int64_t ldc,
-                    void *ws, hipStream_t s) {
+hipError_t gemm_f64(int ta, int tb, int m, int n, int k, const double *A, int64_t lda, const double *B,
+                    int64_t ldb, double *C, int64_t ldc, void *ws, hipStream_t s) {
     if (m == 0 || n == 0) return hipSuccess;
     int nz = gemm_splits(m, n, k);
     int kslice = (k + nz - 1) / nz;
@@ -281,13 +275,13 @@ hipError_t gemm_f64(int ta, int tb, int m, int n, int k, double alpha, const dou
     hipError_t ea = hipFuncSetAttribute((const void *)gemm_f64_kernel,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)GEMM_LDS);
     if (ea != hipSuccess) return ea;
-    hipLaunchKernelGGL(gemm_f64_kernel, grid, dim3(256), GEMM_LDS, s, ta, tb, m, n, k, alpha, A, lda, B,
-                       ldb, beta, C, ldc, kslice, part);
+    hipLaunchKernelGGL(gemm_f64_kernel, grid, dim3(256), GEMM_LDS, s, ta, tb, m, n, k, A, lda, B,
+                       ldb, C, ldc, kslice, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nz == 1) return e;
     int64_t tot = (int64_t)m * n;
     hipLaunchKernelGGL(gemm_f64_reduce_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, m,
-                       n, nz, part, alpha, beta, C, ldc);
+                       n, nz, part, C, ldc);
     return hipGetLastError();
 }
 

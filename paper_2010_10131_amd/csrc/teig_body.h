@@ -1270,7 +1270,7 @@ __device__ void teig_body(const double *__restrict__ S, int64_t lds, int n, int 
             }
             __syncthreads();
         }
-        if (n >= 3 && wave == 0) {
+        if (wave == 0) {
             // p and K of the last step (n - 3)
             const double taup = s_tau[n - 3];
             const double *vp = s_v + ((n - 3) & 1) * n;
@@ -1286,21 +1286,13 @@ __device__ void teig_body(const double *__restrict__ S, int64_t lds, int n, int 
             Kprev = 0.5 * taup * te_wave_sum(t);
         }
         if (tid == 0) {
-            if (n >= 3) {
-                // the last 2 x 2 block with the update of step n - 3
-                const double *v = s_v + ((n - 3) & 1) * n;
-                const double v1 = v[n - 2], v2 = v[n - 1];
-                const double w1 = s_p[n - 2] - Kprev * v1, w2 = s_p[n - 1] - Kprev * v2;
-                s_d[n - 2] = A[(n - 2) + (int64_t)n * (n - 2)] - 2.0 * v1 * w1;
-                s_e[n - 2] = A[(n - 1) + (int64_t)n * (n - 2)] - (v2 * w1 + w2 * v1);
-                s_d[n - 1] = A[(n - 1) + (int64_t)n * (n - 1)] - 2.0 * v2 * w2;
-            } else if (n == 2) {
-                s_d[0] = A[0];
-                s_e[0] = A[1];
-                s_d[1] = A[3];
-            } else {
-                s_d[0] = A[0];
-            }
+            // the last 2 x 2 block with the update of step n - 3
+            const double *v = s_v + ((n - 3) & 1) * n;
+            const double v1 = v[n - 2], v2 = v[n - 1];
+            const double w1 = s_p[n - 2] - Kprev * v1, w2 = s_p[n - 1] - Kprev * v2;
+            s_d[n - 2] = A[(n - 2) + (int64_t)n * (n - 2)] - 2.0 * v1 * w1;
+            s_e[n - 2] = A[(n - 1) + (int64_t)n * (n - 2)] - (v2 * w1 + w2 * v1);
+            s_d[n - 1] = A[(n - 1) + (int64_t)n * (n - 1)] - 2.0 * v2 * w2;
         }
         __syncthreads();
     }
@@ -1393,7 +1385,7 @@ __device__ void teig_body(const double *__restrict__ S, int64_t lds, int n, int 
             for (int pass = 0; pass < 2; ++pass) {
                 const double inv = te_rcp(sqrt(nrm2));
                 // forward elimination with partial pivoting: U rows (1 / u0, u1, u2) to F, y to Z
-                double cd = s_d[0] - lm, cu = n > 1 ? s_e[0] : 0.0, cb = Zr[r] * inv;
+                double cd = s_d[0] - lm, cu = s_e[0], cb = Zr[r] * inv;
 #pragma unroll 4
                 for (int i = 0; i + 1 < n; ++i) {
                     const double sub = s_e[i], nd = s_d[i + 1] - lm, nu = i + 2 < n ? s_e[i + 1] : 0.0;
