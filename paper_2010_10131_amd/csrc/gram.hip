@@ -76,16 +76,16 @@ __global__ __launch_bounds__(SK_T) void gram_skinny_kernel(const float *__restri
 // fewer than waves, ks groups of waves split a block's rows and are summed at the
 // end.  Two stages of loads are in flight, of at most TRI_STAGE values each: a
 // stage costs a barrier and a trip through LDS whatever it holds, so short rows
-// take more of them at a time (see tri_sc).  Float data is widened as it is stored (widened as it is read, once per
-// tile and step, 160^4's first mode took 3.2 ms: the conversions and the products
-// share the FP64 units).
+// take more of them at a time (see tri_sc).  Float data is widened as it is stored
+// (widened as it is read, once per tile and step, 160^4's first mode took 3.2 ms:
+// the conversions and the products share the FP64 units).
 //
-// Bound by the FP64 matrix cores (64 cycles a 16 x 16 x 4 product) from about 100
-// rows on, by the reading of Y below.  160^4 with
-// 160 of 4.1 M rows: 2.20 ms (1.6 ms of products), 2.45 in the skinny body, whose
-// loading waves widen and sort fragments beside their products.  The later modes,
-// I = 160 with L = 16, 256, ..: 289 us, 967 in 128 x 128 blocks, which pad the
-// triangle of 55 tiles to 160.  64^3 double: 8 us a mode, 20 in one block of 64
+// Bound from I of about 100 on by the FP64 matrix cores (64 cycles a 16 x 16 x 4
+// product) and the staging that follows a stage's products, below by the reading
+// of Y.  160^4's first mode, 4.1 M rows: 2.16 ms (1.6 ms of products on the fullest
+// SIMD), 2.45 in the skinny body, whose loading waves widen and sort fragments
+// beside their products.  The later modes, I = 160 with L = 16, 256, ..: 290 us
+// together, 967 in 128 x 128 blocks, which pad the triangle of 55 tiles to 160.  64^3 double: 8 us a mode, 20 in one block of 64
 // and few workgroups.
 constexpr int TRI_T = 512, TRI_W = TRI_T / 64;
 constexpr int TRI_SC = 32;      // rows of a stage at least

@@ -624,12 +624,13 @@ __host__ __device__ inline int sk_ns(int64_t I) { return (int)(((I + 15) / 16 + 
 // QUAD: I >= 4, any alignment of the rows.  MS: super tiles per wave (1 where
 // I <= SK_MS1_MAXI).
 //
-// What bounds it: the matrix cores with FP64 products (I = 160), the reading of Y
-// against the splitting of its values into bf16 parts with bf16x6 (I = 48).  48^5
-// in bf16x6 368 us (579), 160^4 in FP64 2.54 ms (2.94): with the selects beside
-// the loads every stage waited out its own loads before it was multiplied; with
-// the loader's tasks on the waves that multiply, the one came after the other; and
-// rows stored four apart met 4-way bank conflicts.
+// What bounds it: the reading of Y against the splitting of its values into bf16
+// parts with bf16x6 (I = 48); the matrix cores with FP32 products and with FP64 ones
+// (these in the batch only, gram_tri64_kernel takes them elsewhere).  48^5 in bf16x6
+// 351 us (579): with the selects beside the loads every stage waited out its own
+// loads before it was multiplied; with the loader's tasks on the waves that
+// multiply, the one came after the other; and rows stored four apart met 4-way bank
+// conflicts.
 template <int PREC, int CH, bool QUAD, int MS>
 __device__ __forceinline__ void gram_skinny_body(const float *__restrict__ Y, int I, int64_t P, int nkc, int kc,
                                                  double *__restrict__ partials) {

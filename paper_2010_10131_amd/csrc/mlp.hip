@@ -62,8 +62,9 @@ __global__ void mlp_forward_kernel(const float *__restrict__ w, int64_t B, const
 // LDS as broadcasts.  Then the 256 threads each own 4 entries of the W2
 // gradient (and their share of the rest) and sum delta x activation over the
 // MS samples from LDS.  The gradient kept in one thread per parameter, each
-// walking all samples serially in 6 workgroups, took 1505 us of a 1.55 ms
-// step at 4499 samples; the whole step (this, the reduction, Adam) takes 23 us.
+// walking all samples serially in 6 workgroups, took nearly all of a
+// 1507 us step at 4499 samples; the whole step (this, the reduction, Adam) takes
+// 24 us.
 // MS = 32: 16 samples doubles the partial gradients to write and read, 64
 // leaves half the chip without a workgroup at a few thousand samples.
 constexpr int MS = 32, MG = 256 / NH;
