@@ -45,8 +45,8 @@ TTM_PMC = {"ttm": "bf16x3", "fetch_kib": 262941.2, "fetch_scale": 2.000,
 # The same two passes over the skinny mode-1 Grams (bf16x3 products) of the
 # 160^4 and 48^5 workloads: KiB per dispatch, same scales.  Source:
 # profiles/gram_skinny_mode1_hbm_traffic.md.  Valid only for that kernel as it is.
-SKINNY_PMC = {"c3_160pow4_fp32": {"fetch_kib": 1280073.0, "write_kib": 30720.0},
-              "c5_48pow5_fp32": {"fetch_kib": 497765.0, "write_kib": 6144.0}}
+SKINNY_PMC = {"c3_160pow4_fp32": {"fetch_kib": 1280072.5, "write_kib": 30727.5},
+              "c5_48pow5_fp32": {"fetch_kib": 497742.5, "write_kib": 6144.0}}
 
 
 def skinny_traffic(workload, prec, us):
